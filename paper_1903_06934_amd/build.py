@@ -13,7 +13,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIBRARY = os.path.join(PKG, "libmiconv.so")
-SOURCES = ["api.hip", "conv_kernels.hip", "pool_kernels.hip"]
+SOURCES = ["api.hip", "conv_kernels.hip", "wino_kernels.hip",
+           "pool_kernels.hip"]
 PEAK_LIBRARY = os.path.join(PKG, "libmipeak.so")
 PEAK_SOURCES = ["peaks.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

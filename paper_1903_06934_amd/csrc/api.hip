@@ -312,7 +312,11 @@ struct ImgPlan {
     int tw = 0;                // 16-channel blocks per split, tw the pixel-block width
     int th = 0;                // pixel-block rows: 0 for 112 / tw, else a whole th x tw map
     int ks = 1;                // halo wave groups: 2 = eight waves over two halves of the blocks
+    int wino = 0;              // fast filtering: WINO_RULE (the fields above are the direct plan
+                               // behind it) or WINO_PLAN
+    bool plain = false;        // the rule's direct plan as a candidate of its own
 };
+enum { WINO_RULE = 1, WINO_PLAN };
 
 // Rows and columns (pixels rounded up to 16) of a halo pixel block.
 int halo_th(int tw, int th) { return th ? th : kHaloCols / tw; }
@@ -355,7 +359,8 @@ ImgPlan img_rule(int M, long long Ncol, int Kred, int G, bool allow_split)
 bool same_img(const ImgPlan &a, const ImgPlan &b)
 {
     return a.tile == b.tile && a.nsplit == b.nsplit && a.xnb == b.xnb && a.bt == b.bt &&
-           a.halo == b.halo && a.tw == b.tw && a.th == b.th && a.ks == b.ks;
+           a.halo == b.halo && a.tw == b.tw && a.th == b.th && a.ks == b.ks &&
+           (a.wino == WINO_PLAN) == (b.wino == WINO_PLAN) && a.plain == b.plain;
 }
 
 // ------------------------------------------------------------ halo plans
@@ -547,6 +552,63 @@ bool halo_rule(int M, int cin, int nimg, int Pout, int Qout, int src_w, int R, i
     return true;
 }
 
+// ------------------------------------------------------------ fast filtering
+// Stride-1 3 x 3 layers by F(2x2, 3x3) (wino_kernels.hip): M rows over cin
+// source channels per group, all images in one launch.
+bool wino_applies(const Geom &g, int M, int cin)
+{
+    return g.R == 3 && g.S == 3 && g.st == 1 && cin % 8 == 0 && images_per_launch(g) >= g.N &&
+           (long long)wino_filter_words(M, cin, g.G) <= kMaxChunkElems;
+}
+
+// The built-in rule's use of it.  Its GEMM runs in stages (64 rows x 64 tiles
+// x 8 channels); below some number of them its three launches cost more than
+// the direct plan's two, unless the reduction is long, which the direct plans
+// run on few workgroups and this one cuts over all of them.  Measured on the
+// MI355X (direct / fast time, forward and backward-data alike): 64 channels on
+// 56 x 56 maps 0.83 at 784 stages, 1.05 at 1568, 1.35 at 3136; 32 to 64
+// channels 0.85 at 392, 1.02-1.19 at 784-1568; 96 to 128 channels on 28 x 28
+// 0.97 at 1176, 1.24 at 2352; with 128 channels and more 1.1-1.8 from 32
+// stages on (512 on 7 x 7: 1.0-1.1); VGG-16 conv1_2 ... conv5_3 at batch 32
+// 1.6-1.9, ResNet-50's 3 x 3 layers at batch 64 1.4-1.7, AlexNet conv3-conv5
+// 1.4-1.5.  Fewer than 32 rows leave most of a 64-row tile idle; with fewer
+// than 32 channels the transforms' rounding is no longer small beside the
+// sums' (error against 64 bits at 16 channels: equal to the direct plans').
+bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout)
+{
+    if (cin < 32 || M < 32 || !wino_applies(g, M, cin))
+        return false;
+    if (cin >= 128 && M >= 64)
+        return true;
+    const long long tiles = (long long)g.N * ((Pout + 1) / 2) * ((Qout + 1) / 2);
+    return (long long)g.G * ((M + 63) / 64) * ((tiles + 63) / 64) * (cin / 8) >= 6 * num_cus();
+}
+
+// The flag, the transformed filters, the slabs of cut tiles.
+size_t wino_ws(const Geom &g, int M, int cin, int Pout, int Qout)
+{
+    return kAlign + align_up(wino_filter_words(M, cin, g.G) * sizeof(float)) +
+           wino_plan(M, cin, g.G, g.N, Pout, Qout, num_cus()).slab_bytes;
+}
+
+// Candidates after the direct ones: fast filtering where the rule does not
+// take it already, else the rule's direct plan.
+template <class P, class Make>
+void wino_variants(const ImgPlan &rule, bool applies, Make make, std::vector<P> &out)
+{
+    if (rule.wino == WINO_RULE) {
+        ImgPlan d = rule;
+        d.wino = 0;
+        d.plain = true;
+        out.push_back(make(d));
+    } else if (applies) {
+        ImgPlan f{};
+        f.nsplit = 1;
+        f.wino = WINO_PLAN;
+        out.push_back(make(f));
+    }
+}
+
 // ------------------------------------------------------------ inner product
 // A layer of 1 x 1 images and 1 x 1 filters is an inner-product layer
 // (Sec. IV-A): y[n][k] = b[k] + sum_c w[k][c] x[n][c].  Its GEMMs have the
@@ -690,10 +752,13 @@ ImgPlan fwd_rule(const Geom &g)
     }
     ImgPlan h;
     const int nb = images_per_launch(g);
-    if (halo_filter(g) && halo_rule(g.Kg, g.Cg, g.N < nb ? g.N : nb, g.P, g.Q, g.W, g.R, g.G, &h))
-        return h;
-    return img_rule(g.Kg, (long long)(g.N < nb ? g.N : nb) * g.P * g.Q, g.Cg * g.R * g.S, g.G,
-                    nb >= g.N);
+    if (!halo_filter(g) ||
+        !halo_rule(g.Kg, g.Cg, g.N < nb ? g.N : nb, g.P, g.Q, g.W, g.R, g.G, &h))
+        h = img_rule(g.Kg, (long long)(g.N < nb ? g.N : nb) * g.P * g.Q, g.Cg * g.R * g.S, g.G,
+                     nb >= g.N);
+    if (wino_rule(g, g.Kg, g.Cg, g.P, g.Q))
+        h.wino = WINO_RULE;
+    return h;
 }
 
 void fwd_candidates(const Geom &g, std::vector<ImgPlan> &out)
@@ -722,10 +787,14 @@ void fwd_candidates(const Geom &g, std::vector<ImgPlan> &out)
         e.xnb = xnb;
         out.push_back(e);
     }
+    wino_variants<ImgPlan>(out[0], wino_applies(g, g.Kg, g.Cg),
+                           [](const ImgPlan &p) { return p; }, out);
 }
 
 size_t fwd_ws(const Geom &g, const ImgPlan &p)
 {
+    if (p.wino)
+        return wino_ws(g, g.Kg, g.Cg, g.P, g.Q);
     if (p.bt)
         return (ip_packs_w(g, p.tile) ? fwd_pack_bytes(g) : 0) +
                align_up((size_t)g.C * g.N * sizeof(float)) +
@@ -737,10 +806,23 @@ size_t fwd_ws(const Geom &g, const ImgPlan &p)
     return fwd_pack_bytes(g) + part;
 }
 
+void append_name(const char *text, char *buf, size_t len)
+{
+    const size_t n = strlen(buf);
+    snprintf(buf + n, len - n, "%s", text);
+}
+
 void fwd_name(const ImgPlan &p, char *buf, size_t len)
 {
     const char *pre = p.bt ? "batch-transposed, " : "";
-    if (p.xnb > 0)
+    if (p.plain) {
+        ImgPlan d = p;
+        d.plain = false;
+        fwd_name(d, buf, len);
+        append_name(", products summed directly", buf, len);
+    } else if (p.wino == WINO_PLAN)
+        snprintf(buf, len, "fast filtering of 2x2 tiles");
+    else if (p.xnb > 0)
         snprintf(buf, len, "explicit im2col (%d images a chunk), image GEMM %s", p.xnb,
                  img_tile_name(p.tile));
     else if (p.halo >= 0 && p.nsplit > 1)
@@ -886,6 +968,8 @@ BwdPlan bwd_rule(const Geom &g)
     } else {
         p.img = ImgPlan{-1, 1, 0};
     }
+    if (!p.bt && !p.blocked && wino_rule(g, g.Cg, g.Kg, g.H, g.W))
+        p.img.wino = WINO_RULE;
     return p;
 }
 
@@ -932,6 +1016,8 @@ void bwd_candidates(const Geom &g, std::vector<BwdPlan> &out)
         e.img = with_split(pick_img_tile(crs, (long long)xnb * g.P * g.Q, g.Kg, g.G), g.Kg, 1);
         out.push_back(e);
     }
+    wino_variants<BwdPlan>(out[0].img, wino_applies(g, g.Cg, g.Kg),
+                           [](const ImgPlan &i) { return BwdPlan{false, BlockPlan{}, i, 0}; }, out);
 }
 
 size_t bwd_ws(const Geom &g, const BwdPlan &p)
@@ -947,6 +1033,8 @@ size_t bwd_ws(const Geom &g, const BwdPlan &p)
                col_bytes(g, p.xnb);
     if (p.blocked)
         return align_up((size_t)g.G * p.bp.M * p.bp.a_ld * sizeof(float));
+    if (p.img.wino)
+        return wino_ws(g, g.Cg, g.Kg, g.H, g.W);
     size_t total = 0;
     for (int ph = 0; ph < g.st; ph++)
         for (int pw = 0; pw < g.st; pw++) {
@@ -961,7 +1049,14 @@ size_t bwd_ws(const Geom &g, const BwdPlan &p)
 
 void bwd_name(const BwdPlan &p, char *buf, size_t len)
 {
-    if (p.bt && p.img.nsplit > 1)
+    if (p.img.plain) {
+        BwdPlan d = p;
+        d.img.plain = false;
+        bwd_name(d, buf, len);
+        append_name(", products summed directly", buf, len);
+    } else if (p.img.wino == WINO_PLAN)
+        snprintf(buf, len, "fast filtering of 2x2 tiles");
+    else if (p.bt && p.img.nsplit > 1)
         snprintf(buf, len, "batch-transposed, image GEMM %s, %d splits", img_tile_name(p.img.tile),
                  p.img.nsplit);
     else if (p.bt)
@@ -1468,6 +1563,45 @@ int halo_gemm(const ImgPlan &plan, int M, int groups, const float *A, int a_ld, 
     return launch_status(launch_halo_gemm(h, plan.halo, flip, stream));
 }
 
+// Fast filtering (plan.wino): the transformed filters into ws, then one GEMM
+// launch.  M rows, cin source channels; flip for backward-data.
+int wino_exec(const Geom &g, int M, int cin, const float *src, int src_h, int src_w, int Pout,
+              int Qout, int off, bool flip, const float *w, const float *bias, float *out,
+              void *ws, hipStream_t stream)
+{
+    const size_t fb = sizeof(float);
+    const size_t u_bytes = wino_filter_words(M, cin, g.G) * fb;
+    float *U = (float *)((char *)ws + kAlign);
+    WinoArgs a{};
+    a.M = M;
+    a.cin = cin;
+    a.groups = g.G;
+    a.nimg = g.N;
+    a.w = w;
+    a.flip = flip;
+    a.u_bytes = (uint32_t)u_bytes;
+    a.src = src;
+    a.src_hw = src_h * src_w;
+    a.src_h = src_h;
+    a.src_w = src_w;
+    a.src_img_words = (uint32_t)((size_t)g.G * cin * a.src_hw);
+    a.src_bytes = (uint32_t)((size_t)g.N * a.src_img_words * fb);
+    a.P = Pout;
+    a.Q = Qout;
+    a.off = off;
+    a.out = out;
+    a.bias = bias;
+    a.out_hw = Pout * Qout;
+    a.out_img_stride = (long long)g.G * M * a.out_hw;
+    a.out_bytes = (uint32_t)((size_t)g.N * a.out_img_stride * fb);
+    a.flag = (int *)ws;
+    a.slabs = (float *)((char *)U + align_up(u_bytes));
+    a.before = tl_events.before;
+    a.after = tl_events.after;
+    return launch_status(
+        launch_wino(a, wino_plan(M, cin, g.G, g.N, Pout, Qout, num_cus()), U, stream));
+}
+
 // Forward GEMM launches over n images of geometry g (images from src, outputs
 // to y), at most images_per_launch(g) images a launch; wp is the packed
 // filter bank, part the split-K slabs (plan.nsplit > 1: n must be all of g's).
@@ -1657,7 +1791,7 @@ int ip_bwd_data(const Geom &g, const BwdPlan &plan, const float *dy, const float
     return MICONV_OK;
 }
 
-int fwd_exec(const Geom &g, const ImgPlan &plan, const float *x, const float *w, const float *b,
+int fwd_exec(const Geom &g, ImgPlan plan, const float *x, const float *w, const float *b,
              float *y, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const int N = g.N, C = g.C, H = g.H, W = g.W, K = g.K, R = g.R, S = g.S;
@@ -1668,11 +1802,18 @@ int fwd_exec(const Geom &g, const ImgPlan &plan, const float *x, const float *w,
                   {y, (size_t)N * K * g.P * g.Q * fb, true}};
     bool req[4] = {true, true, false, true};
     int st = check_buffers(r, 4, req, ws, ws_bytes, fwd_ws(g, plan));
+    if (st != MICONV_OK && plan.wino == WINO_RULE) {
+        // What the direct plan accepts stays accepted (a smaller workspace).
+        plan.wino = 0;
+        st = check_buffers(r, 4, req, ws, ws_bytes, fwd_ws(g, plan));
+    }
     if (st != MICONV_OK || (st = check_device()) != MICONV_OK)
         return st;
     (void)hipGetLastError();
     if (plan.bt)
         return ip_fwd(g, plan, x, w, b, y, ws, stream);
+    if (plan.wino)
+        return wino_exec(g, g.Kg, g.Cg, x, H, W, g.P, g.Q, -g.pad, false, w, b, y, ws, stream);
 
     // The filter bank, packed in the layout the tile reads.  The explicit
     // plan's 1x1 GEMM reads the same matrix: its reduction index is the
@@ -1878,7 +2019,7 @@ int phase_gemms(const Geom &g, const BwdPlan &plan, const float *w, char *&wsp, 
     return MICONV_OK;
 }
 
-int bwd_exec(const Geom &g, const BwdPlan &plan, const float *dy, const float *w, float *dx,
+int bwd_exec(const Geom &g, BwdPlan plan, const float *dy, const float *w, float *dx,
              void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const int N = g.N, C = g.C, H = g.H, W = g.W, K = g.K, R = g.R, S = g.S;
@@ -1888,6 +2029,10 @@ int bwd_exec(const Geom &g, const BwdPlan &plan, const float *dy, const float *w
                   {dx, (size_t)N * C * H * W * fb, true}};
     bool req[3] = {true, true, true};
     int st = check_buffers(r, 3, req, ws, ws_bytes, bwd_ws(g, plan));
+    if (st != MICONV_OK && plan.img.wino == WINO_RULE) {
+        plan.img.wino = 0;
+        st = check_buffers(r, 3, req, ws, ws_bytes, bwd_ws(g, plan));
+    }
     if (st != MICONV_OK || (st = check_device()) != MICONV_OK)
         return st;
     (void)hipGetLastError();
@@ -1895,6 +2040,9 @@ int bwd_exec(const Geom &g, const BwdPlan &plan, const float *dy, const float *w
         return bwd_blocked(g, plan, dy, w, dx, ws, stream);
     if (plan.bt)
         return ip_bwd_data(g, plan, dy, w, dx, ws, stream);
+    if (plan.img.wino)
+        return wino_exec(g, g.Cg, g.Kg, dy, g.P, g.Q, H, W, g.pad - 2, true, w, nullptr, dx, ws,
+                         stream);
 
     const long long xi = (long long)C * H * W, yi = (long long)K * g.P * g.Q;
     bool marked = false;
@@ -2149,13 +2297,35 @@ int candidate_count(int pass, const Geom &g)
     }
 }
 
-size_t candidate_ws(int pass, const Geom &g, int index)
+// Workspace with which a plan runs as it does with any larger one (the rule's
+// fast filtering: the larger of its own and the direct plan's), and the least
+// with which it runs at all (the smaller).
+size_t fwd_need(const Geom &g, ImgPlan p, bool least = false)
+{
+    size_t n = fwd_ws(g, p);
+    if (p.wino == WINO_RULE) {
+        p.wino = 0;
+        n = least ? std::min(n, fwd_ws(g, p)) : std::max(n, fwd_ws(g, p));
+    }
+    return n;
+}
+size_t bwd_need(const Geom &g, BwdPlan p, bool least = false)
+{
+    size_t n = bwd_ws(g, p);
+    if (p.img.wino == WINO_RULE) {
+        p.img.wino = 0;
+        n = least ? std::min(n, bwd_ws(g, p)) : std::max(n, bwd_ws(g, p));
+    }
+    return n;
+}
+
+size_t candidate_ws(int pass, const Geom &g, int index, bool least = false)
 {
     switch (pass) {
     case MICONV_PASS_FWD:
-        return fwd_ws(g, pick(fwd_rule(g), index, fwd_candidates, g));
+        return fwd_need(g, pick(fwd_rule(g), index, fwd_candidates, g), least);
     case MICONV_PASS_BWD_DATA:
-        return bwd_ws(g, pick(bwd_rule(g), index, bwd_candidates, g));
+        return bwd_need(g, pick(bwd_rule(g), index, bwd_candidates, g), least);
     case MICONV_PASS_BWD_WEIGHT:
         return wgrad_ws(g, pick(wgrad_rule(g), index, wgrad_candidates, g));
     default:
@@ -2172,14 +2342,14 @@ size_t max_candidate_ws(int pass, const Geom &g)
         std::vector<ImgPlan> c;
         fwd_candidates(g, c);
         for (const ImgPlan &p : c)
-            need = std::max(need, fwd_ws(g, p));
+            need = std::max(need, fwd_need(g, p));
         break;
     }
     case MICONV_PASS_BWD_DATA: {
         std::vector<BwdPlan> c;
         bwd_candidates(g, c);
         for (const BwdPlan &p : c)
-            need = std::max(need, bwd_ws(g, p));
+            need = std::max(need, bwd_need(g, p));
         break;
     }
     case MICONV_PASS_BWD_WEIGHT: {
@@ -2514,7 +2684,7 @@ int conv_tune(int pass, int N, int C, int H, int W, int K, int R, int S, int str
     tl_events = TimingEvents{};
     std::vector<int> fit;
     for (int i = 0; i < n; i++)
-        if (candidate_ws(pass, g, i) <= ws_bytes)
+        if (candidate_ws(pass, g, i, true) <= ws_bytes)
             fit.push_back(i);
     std::vector<hipEvent_t> ev(2 * reps, nullptr);
     for (auto &e : ev)

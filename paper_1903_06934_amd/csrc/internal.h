@@ -181,6 +181,49 @@ struct WgradHaloArgs {
 bool wgrad_halo_supported(int TW, int P, int Q, int W);
 hipError_t launch_wgrad_halo(const WgradHaloArgs &a, hipStream_t stream);
 
+// ---------------------------------------------------------------------------
+// Fast filtering F(2x2, 3x3) of a stride-1 3 x 3 problem (forward, or the one
+// phase of backward-data): M rows per group (output channels), cin source
+// channels per group (a multiple of 8), output grid P x Q of 2 x 2 tiles whose
+// 4 x 4 source patch starts at (2 ty + off, 2 tx + off), zero outside the
+// source.  Tiles are numbered over (image, tile row, tile column); an output
+// tile of the GEMM is 64 rows x 64 tiles, numbered tiles fastest.
+// ---------------------------------------------------------------------------
+struct WinoArgs {
+    int M, cin, groups, nimg;
+    const float *w;            // the layer's filters
+    int flip;                  // backward-data: rows are input channels, taps mirrored
+    uint32_t u_bytes;
+    const float *src;
+    uint32_t src_bytes;
+    int src_h, src_w, src_hw;
+    uint32_t src_img_words;
+    int P, Q, off;
+    float *out;
+    const float *bias;         // may be null
+    long long out_img_stride;
+    int out_hw;
+    uint32_t out_bytes;        // < 2^31
+    int *flag;                 // raised when an output is not finite
+    float *slabs;              // partial sums of cut output tiles, 64 KiB each
+    hipEvent_t before, after;  // recorded around the GEMM (may be null)
+    // Set by launch_wino:
+    const float *U;
+    int Pt, Qt, tiles, tblocks, mblocks, nstage, nwg, rounds, rest;
+    int share, share_rem;      // stages of the remaining tiles: per workgroup, left over
+    FastDiv d_pt, d_qt, d_nstage, d_tblocks, d_mblocks;
+};
+// nwg workgroups take `rounds` whole output tiles each; the `rest` remaining
+// ones are cut along the channels into equal shares.
+struct WinoPlan {
+    int nwg, rounds, rest;
+    size_t slab_bytes;
+};
+size_t wino_filter_words(int M, int cin, int groups);
+WinoPlan wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus);
+// Filter transform (into U), GEMM and finish.
+hipError_t launch_wino(WinoArgs a, const WinoPlan &p, float *U, hipStream_t stream);
+
 // Image-GEMM tile shapes (BM x BN; 4 waves, 3 for 48x64).
 enum ImgTile {
     IMG_64x64 = 0, IMG_128x64, IMG_16x128, IMG_32x64, IMG_48x64, IMG_96x64, IMG_96x128,

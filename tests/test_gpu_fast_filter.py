@@ -1,0 +1,166 @@
+"""Fast filtering F(2x2, 3x3) of stride-1 3x3 layers (forward and
+backward-data) against the oracle, at the sizes where its tiling can go wrong,
+with infinities and NaNs, and with workspaces that only hold the direct plan."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_util import assert_within, dev, host
+
+pytestmark = pytest.mark.gpu
+
+# (N, C, H, W, K, 3, 3, 1, pad, G).  A GEMM tile is 64 rows x 64 tiles of 2 x 2
+# pixels, a stage 8 channels, a workgroup's share at least 4 stages; source
+# columns load in pairs on even widths (from odd or even offsets), singly on
+# odd ones.
+SHAPES = [
+    (1, 8, 3, 3, 8, 3, 3, 1, 1, 1),        # one stage, one 2 x 2 grid of tiles, odd edges
+    (1, 8, 2, 2, 5, 3, 3, 1, 2, 1),        # 4 x 4 outputs of a 2 x 2 image
+    (2, 16, 14, 14, 64, 3, 3, 1, 1, 1),    # 98 tiles: a ragged second block
+    (3, 24, 13, 13, 72, 3, 3, 1, 1, 1),    # odd map, rows past one 64-row block
+    (2, 40, 9, 12, 130, 3, 3, 1, 0, 1),    # pad 0, even width
+    (2, 32, 7, 9, 48, 3, 3, 1, 2, 1),      # pad 2, odd width
+    (1, 16, 6, 6, 16, 3, 3, 1, 3, 1),      # pad 3: outputs that read only padding
+    (2, 64, 11, 10, 96, 3, 3, 1, 1, 2),    # groups
+    (1, 256, 5, 5, 64, 3, 3, 1, 1, 1),     # one tile cut over 8 workgroups
+    (9, 128, 15, 15, 200, 3, 3, 1, 1, 1),  # 36 tiles of 16 stages over 144 workgroups
+    (1, 8, 258, 259, 64, 3, 3, 1, 1, 1),   # over one round of workgroups, short reductions
+]
+
+
+def _plan(p, shape, want):
+    import paper_1903_06934_amd as m
+    names = [m.plan_name(p, shape, i) for i in range(m.plan_count(p, shape))]
+    direct = [i for i, n in enumerate(names) if n.endswith("products summed directly")]
+    fast = [i for i, n in enumerate(names) if n.startswith("fast filtering")]
+    assert len(direct) + len(fast) <= 1  # the rule takes one of the two, the list names the other
+    if want == "fast":
+        return fast[0] if fast else (0 if direct else None)
+    return direct[0] if direct else 0
+
+
+@pytest.fixture(autouse=True)
+def _clean():
+    import paper_1903_06934_amd as m
+    m.plan_clear()
+    yield
+    m.plan_clear()
+
+
+def _run(p, shape, t, ws=None):
+    import paper_1903_06934_amd as m
+    N, C, H, W, K, R, S, st, pad, G = shape
+    if p == m.PASS_FWD:
+        return m.conv_fwd(t["x"], t["w"], t["b"], st, pad, G, ws=ws)
+    return m.conv_bwd_data(t["dy"], t["w"], (H, W), st, pad, G, ws=ws)
+
+
+def _inputs(shape, seed):
+    N, C, H, W, K, R, S, st, pad, G = shape
+    P, Q = oracle.out_size(H, R, st, pad), oracle.out_size(W, S, st, pad)
+    return workloads.make_inputs(shape, P, Q, seed=seed, init="he")
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_matches_oracle(shape):
+    import paper_1903_06934_amd as m
+    d = _inputs(shape, (71, 1))
+    t = {k: dev(v) for k, v in d.items()}
+    refs = (oracle.conv_fwd(shape, d["x"], d["w"], d["b"]),
+            oracle.conv_bwd_data(shape, d["dy"], d["w"]))
+    ran = 0
+    for p in (m.PASS_FWD, m.PASS_BWD_DATA):
+        i = _plan(p, shape, "fast")
+        if i is None:  # the pass's source channels are no multiple of 8
+            continue
+        m.plan_set(p, shape, i)
+        got = host(_run(p, shape, t))
+        assert_within(got, refs[p][0], refs[p][1], f"pass {p}")
+        again = host(_run(p, shape, t))
+        assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
+        ran += 1
+    assert ran
+
+
+@pytest.mark.parametrize("shape", [(2, 128, 14, 14, 64, 3, 3, 1, 1, 1),
+                                   (1, 256, 6, 7, 64, 3, 3, 1, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_infinities_and_nans_as_the_direct_plan(shape):
+    """The transforms mix a tile's pixels; outputs that come out non-finite are
+    recomputed directly, so an infinity or a NaN reaches exactly the outputs
+    that it reaches in the direct plan, and the others stay within the bar."""
+    import paper_1903_06934_amd as m
+    d = _inputs(shape, (72, 1))
+    x = d["x"].copy()
+    x[0, 3, 2, 2], x[0, 5, 5, 1], x[0, 7, 0, 6] = np.inf, -np.inf, np.nan
+    x[0, 9, 4, 4] = x[0, 9, 4, 5] = 3e38  # the transform overflows, the sums do not
+    w = d["w"].copy()
+    w[:, 9] *= 1e-3
+    t = {"x": dev(x), "w": dev(w), "b": dev(d["b"])}
+    got = {}
+    for want in ("fast", "direct"):
+        m.plan_set(m.PASS_FWD, shape, _plan(m.PASS_FWD, shape, want))
+        got[want] = host(_run(m.PASS_FWD, shape, t))
+    a, b = got["fast"], got["direct"]
+    assert np.array_equal(np.isnan(a), np.isnan(b))
+    assert np.array_equal(np.isposinf(a), np.isposinf(b))
+    assert np.array_equal(np.isneginf(a), np.isneginf(b))
+    fin = np.isfinite(b)
+    assert 0 < (~fin).sum() < fin.size
+    x0 = np.where(np.isfinite(x), x, 0).astype(np.float32)
+    ref, absum = oracle.conv_fwd(shape, x0, w, d["b"])
+    assert_within(a[fin], ref[fin], absum[fin], "finite outputs")
+
+
+def test_smaller_workspace_runs_the_direct_plan():
+    """Where the workspace holds the direct plan but not the transformed
+    filters, the rule runs the direct plan, bit for bit."""
+    import torch
+    import paper_1903_06934_amd as m
+    shape = (2, 128, 14, 14, 128, 3, 3, 1, 1, 1)
+    d = _inputs(shape, (73, 1))
+    t = {k: dev(v) for k, v in d.items()}
+    for p in (m.PASS_FWD, m.PASS_BWD_DATA):
+        i = _plan(p, shape, "direct")
+        assert i > 0
+        nbytes = m.plan_workspace_size(p, shape, i)
+        assert nbytes < m.plan_workspace_size(p, shape, 0) <= m.workspace_size(p, shape)
+        small = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        by_rule = host(_run(p, shape, t, ws=small))
+        m.plan_set(p, shape, i)
+        direct = host(_run(p, shape, t, ws=small))
+        m.plan_set(p, shape, 0)
+        assert np.array_equal(by_rule.view(np.uint32), direct.view(np.uint32))
+        assert not np.array_equal(by_rule, host(_run(p, shape, t)))
+        with pytest.raises(m.MiconvError):
+            _run(p, shape, t, ws=torch.empty(nbytes - 256, dtype=torch.uint8, device="cuda"))
+
+
+def test_captured_graph_replays():
+    """The three launches captured; each replay on new inputs, with an eager
+    call between, equals the eager result."""
+    import torch
+    import paper_1903_06934_amd as m
+    shape = (2, 128, 13, 14, 128, 3, 3, 1, 1, 1)
+    t = {k: dev(v) for k, v in _inputs(shape, (74, 1)).items()}
+    ws = torch.empty(m.workspace_size(m.PASS_FWD, shape), dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(t["dy"])
+
+    def call():
+        m.conv_fwd(t["x"], t["w"], t["b"], 1, 1, 1, y=y, ws=ws)
+
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for k in range(3):
+        t["x"].mul_(0.5 + k)
+        y.fill_(float("nan"))
+        g.replay()
+        got = host(y)
+        want = host(m.conv_fwd(t["x"], t["w"], t["b"], 1, 1, 1))
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
