@@ -189,7 +189,7 @@ int conv_set_timing_events(hipEvent_t before, hipEvent_t after);
  *
  * Fast filtering.  Stride-1 3 x 3 layers may also run by minimal filtering
  * (F(2x2, 3x3): 16 multiplications instead of 36 for 2 x 2 outputs and a
- * channel, in fp32 throughout), whose results differ from a direct sum's by
+ * channel, in fp32 throughout; backward-weight F(3x3, 2x2)), whose results differ from a direct sum's by
  * rounding only: less than a direct plan's on dense data; where a layer's
  * filters or inputs cancel or skip products exactly (a filter with a single
  * tap, say), by roundings of the size of the neighbouring products.  Outputs

@@ -588,7 +588,7 @@ bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout)
 size_t wino_ws(const Geom &g, int M, int cin, int Pout, int Qout)
 {
     return kAlign + align_up(wino_filter_words(M, cin, g.G) * sizeof(float)) +
-           wino_plan(M, cin, g.G, g.N, Pout, Qout, num_cus()).slab_bytes;
+           wino_slab_bytes(wino_plan(M, cin, g.G, g.N, Pout, Qout, num_cus()));
 }
 
 // Candidates after the direct ones: fast filtering where the rule does not
@@ -1099,6 +1099,8 @@ struct WgradPlan {
     int halo_tw = 0;  // halo backward-weight with this pixel-block width (0: no); chunk then
                       // counts pixel blocks
     int halo_ct = 1;  // its 16-channel sub-tiles per workgroup (1 or 2)
+    int wino = 0;     // fast filtering, as ImgPlan's
+    bool plain = false;
     int halo_db = 0;  // halo_ct 2: 1 the double-buffered eight-wave kernel, 2 single-stage eight waves
 };
 
@@ -1267,7 +1269,40 @@ WgradPlan wgrad_halo_plan(const Geom &g, int tw, int scale = 0, int ct = 1, int 
     return p;
 }
 
-WgradPlan wgrad_rule(const Geom &g)
+// Fast filtering of backward-weight (wino_wgrad_kernel): stride-1 3 x 3 layers,
+// any channel counts, all images in one launch.
+bool wgrad_wino_applies(const Geom &g)
+{
+    return g.R == 3 && g.S == 3 && g.st == 1 && images_per_launch(g) >= g.N;
+}
+
+size_t wgrad_wino_ws(const Geom &g)
+{
+    int cw;
+    return align_up(wino_wgrad_slab_bytes(
+        wino_wgrad_plan(g.Kg, g.Cg, g.G, g.N, g.P, g.Q, num_cus(), &cw)));
+}
+
+// The built-in rule's use of it: where its 64 x 64 tiles are mostly real, a tile
+// has at least 32 stages (of eight 2 x 2 tiles of dy) to reduce and there are at
+// least 6 stages a CU.  Measured on the MI355X (direct / fast time): VGG-16
+// conv1_2 ... conv4_3 at batch 32 1.6-1.9, conv5_x 1.5; ResNet-50's 3 x 3
+// layers at batch 64 1.2-1.5; AlexNet conv3-conv5 1.4-1.5; 64 to 256 channels
+// at batch 16 1.06-1.16 (1568 stages); 512 channels on 14 x 14 maps 0.84 at
+// batch 4 (24 stages a tile), 1.27 at batch 16; half-empty tiles (32 -> 64
+// channels) 0.93-1.0, 16 -> 16 0.6-0.8.
+bool wgrad_wino_rule(const Geom &g)
+{
+    if (!wgrad_wino_applies(g))
+        return false;
+    int cw;
+    const WinoWork w = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.N, g.P, g.Q, num_cus(), &cw);
+    const long long kb = (g.Kg + 63) / 64, cb = (g.Cg + 63) / 64;
+    return 10LL * g.Kg * g.Cg >= 6 * 4096 * kb * cb && w.nstage >= 32 &&
+           kb * cb * g.G * w.nstage >= 6 * num_cus();
+}
+
+WgradPlan wgrad_direct_rule(const Geom &g)
 {
     // Where the channels allow, 64 x 32 tiles over eight waves: on maps of 112
     // rows or more the double-buffered kernel (VGG-16 at batch 32: conv1_2 ...
@@ -1293,6 +1328,14 @@ WgradPlan wgrad_rule(const Geom &g)
     }
     WgradPlan p = wgrad_plan(batch_columns(g), g.K > 64 && g.K <= 96 ? WG_PIX_96x64 : WG_PIX_64x64);
     p.bt = true;
+    return p;
+}
+
+WgradPlan wgrad_rule(const Geom &g)
+{
+    WgradPlan p = wgrad_direct_rule(g);
+    if (wgrad_wino_rule(g))
+        p.wino = WINO_RULE;
     return p;
 }
 
@@ -1372,10 +1415,23 @@ void wgrad_candidates(const Geom &g, std::vector<WgradPlan> &out)
                     }
         }
     }
+    if (out[0].wino == WINO_RULE) {
+        WgradPlan d = out[0];
+        d.wino = 0;
+        d.plain = true;
+        out.push_back(d);
+    } else if (wgrad_wino_applies(g)) {
+        WgradPlan f{};
+        f.tile = -1;
+        f.wino = WINO_PLAN;
+        out.push_back(f);
+    }
 }
 
 size_t wgrad_ws(const Geom &g, const WgradPlan &p)
 {
+    if (p.wino)
+        return wgrad_wino_ws(g);
     if (p.img >= 0)  // dy^T [K][N]
         return align_up((size_t)g.K * g.N * sizeof(float));
     const size_t bt = p.bt ? align_up((size_t)g.C * g.N * sizeof(float)) +
@@ -1386,7 +1442,14 @@ size_t wgrad_ws(const Geom &g, const WgradPlan &p)
 
 void wgrad_name(const WgradPlan &p, char *buf, size_t len)
 {
-    if (p.img >= 0)
+    if (p.plain) {
+        WgradPlan d = p;
+        d.plain = false;
+        wgrad_name(d, buf, len);
+        append_name(", products summed directly", buf, len);
+    } else if (p.wino == WINO_PLAN)
+        snprintf(buf, len, "fast filtering of 2x2 tiles");
+    else if (p.img >= 0)
         snprintf(buf, len, "batch-transposed, image GEMM %s over the batch", img_tile_name(p.img));
     else if (p.halo_tw)
         snprintf(buf, len, "halo, 9 taps of 64x%d%s (%dx%d pixels), %d splits of %d blocks",
@@ -2121,7 +2184,7 @@ int wgrad_launches(const Geom &g, const WgradPlan &p, const float *x, const floa
     return MICONV_OK;
 }
 
-int wgrad_exec(const Geom &g, const WgradPlan &p, const float *x, const float *dy, float *dw,
+int wgrad_exec(const Geom &g, WgradPlan p, const float *x, const float *dy, float *dw,
                float *db, void *ws, size_t ws_bytes, hipStream_t stream)
 {
     const int N = g.N, C = g.C, H = g.H, W = g.W, K = g.K, R = g.R, S = g.S;
@@ -2132,10 +2195,50 @@ int wgrad_exec(const Geom &g, const WgradPlan &p, const float *x, const float *d
                   {db, (size_t)K * fb, true}};
     bool req[4] = {true, true, true, false};
     int st = check_buffers(r, 4, req, ws, ws_bytes, wgrad_ws(g, p));
+    if (st != MICONV_OK && p.wino == WINO_RULE) {
+        p.wino = 0;
+        st = check_buffers(r, 4, req, ws, ws_bytes, wgrad_ws(g, p));
+    }
     if (st != MICONV_OK || (st = check_device()) != MICONV_OK)
         return st;
     (void)hipGetLastError();
 
+    if (p.wino) {
+        WinoWgArgs a{};
+        a.Kg = g.Kg;
+        a.Cg = g.Cg;
+        a.groups = g.G;
+        a.nimg = N;
+        a.x = x;
+        a.dy = dy;
+        a.x_img_words = (uint32_t)((size_t)C * H * W);
+        a.dy_img_words = (uint32_t)((size_t)K * g.P * g.Q);
+        a.x_bytes = (uint32_t)((size_t)N * a.x_img_words * fb);
+        a.dy_bytes = (uint32_t)((size_t)N * a.dy_img_words * fb);
+        a.H = H;
+        a.W = W;
+        a.HW = H * W;
+        a.P = g.P;
+        a.Q = g.Q;
+        a.PQ = g.P * g.Q;
+        a.off = -g.pad;
+        a.dw = dw;
+        a.db = db;
+        // A stage adds 8 tiles of 4 products.  Accumulated as long as a split
+        // of the direct plan, its sums are off by up to 1.1 times as much
+        // (rectified inputs; VGG-16 conv5_x 5.3e-7 against 4.8e-7 of the
+        // norm), growing with the root of the length: runs of at most 0.7 of
+        // the direct plan's stay below it.
+        const WgradPlan direct = wgrad_direct_rule(g);
+        const long long run = (long long)direct.chunk * (direct.halo_tw ? kHaloCols : 1);
+        a.most = (int)std::max(8LL, run * 7 / 10 / 32);
+        a.slabs = (float *)ws;
+        a.before = tl_events.before;
+        a.after = tl_events.after;
+        int cw;
+        const WinoWork work = wino_wgrad_plan(g.Kg, g.Cg, g.G, N, g.P, g.Q, num_cus(), &cw);
+        return launch_status(launch_wino_wgrad(a, work, cw, stream));
+    }
     if (p.img >= 0) {
         // Inner product, dW [K][C] = sum over n of dy[n][k] x[n][c] as one
         // image GEMM: rows K from dy^T (m-major, the batch as its reduction
@@ -2319,6 +2422,16 @@ size_t bwd_need(const Geom &g, BwdPlan p, bool least = false)
     return n;
 }
 
+size_t wgrad_need(const Geom &g, WgradPlan p, bool least = false)
+{
+    size_t n = wgrad_ws(g, p);
+    if (p.wino == WINO_RULE) {
+        p.wino = 0;
+        n = least ? std::min(n, wgrad_ws(g, p)) : std::max(n, wgrad_ws(g, p));
+    }
+    return n;
+}
+
 size_t candidate_ws(int pass, const Geom &g, int index, bool least = false)
 {
     switch (pass) {
@@ -2327,7 +2440,7 @@ size_t candidate_ws(int pass, const Geom &g, int index, bool least = false)
     case MICONV_PASS_BWD_DATA:
         return bwd_need(g, pick(bwd_rule(g), index, bwd_candidates, g), least);
     case MICONV_PASS_BWD_WEIGHT:
-        return wgrad_ws(g, pick(wgrad_rule(g), index, wgrad_candidates, g));
+        return wgrad_need(g, pick(wgrad_rule(g), index, wgrad_candidates, g), least);
     default:
         return 0;
     }
@@ -2356,7 +2469,7 @@ size_t max_candidate_ws(int pass, const Geom &g)
         std::vector<WgradPlan> c;
         wgrad_candidates(g, c);
         for (const WgradPlan &p : c)
-            need = std::max(need, wgrad_ws(g, p));
+            need = std::max(need, wgrad_need(g, p));
         break;
     }
     default:
@@ -2566,7 +2679,7 @@ int conv_bwd_weight_noalloc(int N, int C, int H, int W, int K, int R, int S, int
     if (st != MICONV_OK)
         return st;
     const WgradPlan p = wgrad_current(g);
-    if (wgrad_ws(g, p) > kScratchBytes)
+    if (wgrad_need(g, p, true) > kScratchBytes)
         return MICONV_ERR_SCRATCH;
     if ((st = check_device()) != MICONV_OK)
         return st;

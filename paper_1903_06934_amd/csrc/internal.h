@@ -189,7 +189,15 @@ hipError_t launch_wgrad_halo(const WgradHaloArgs &a, hipStream_t stream);
 // source.  Tiles are numbered over (image, tile row, tile column); an output
 // tile of the GEMM is 64 rows x 64 tiles, numbered tiles fastest.
 // ---------------------------------------------------------------------------
-struct WinoArgs {
+// Work split of a persistent GEMM: nwg workgroups take `rounds` whole output
+// tiles each; the `rest` remaining ones, nstage stages each, are cut along the
+// reduction into equal shares, whose partial sums go to slabs.
+struct WinoWork {
+    int nwg, rounds, rest, nstage;
+    int share, share_rem;      // stages of the remaining tiles: per workgroup, left over
+    FastDiv d_nstage;
+};
+struct WinoArgs : WinoWork {
     int M, cin, groups, nimg;
     const float *w;            // the layer's filters
     int flip;                  // backward-data: rows are input channels, taps mirrored
@@ -209,20 +217,38 @@ struct WinoArgs {
     hipEvent_t before, after;  // recorded around the GEMM (may be null)
     // Set by launch_wino:
     const float *U;
-    int Pt, Qt, tiles, tblocks, mblocks, nstage, nwg, rounds, rest;
-    int share, share_rem;      // stages of the remaining tiles: per workgroup, left over
-    FastDiv d_pt, d_qt, d_nstage, d_tblocks, d_mblocks;
-};
-// nwg workgroups take `rounds` whole output tiles each; the `rest` remaining
-// ones are cut along the channels into equal shares.
-struct WinoPlan {
-    int nwg, rounds, rest;
-    size_t slab_bytes;
+    int Pt, Qt, tiles, tblocks, mblocks;
+    FastDiv d_pt, d_qt, d_tblocks, d_mblocks;
 };
 size_t wino_filter_words(int M, int cin, int groups);
-WinoPlan wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus);
+WinoWork wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus);
+size_t wino_slab_bytes(const WinoWork &w);
 // Filter transform (into U), GEMM and finish.
-hipError_t launch_wino(WinoArgs a, const WinoPlan &p, float *U, hipStream_t stream);
+hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stream);
+
+// ---------------------------------------------------------------------------
+// Backward-weight of the same layers by F(3x3, 2x2): 2 x 2 tiles of dy, 4 x 4
+// patches of x at (2 ty + off, 2 tx + off) with off = -pad; an output tile is
+// 64 filters x 64 channels of a group (channels fastest), its reduction the
+// tiles in stages of eight: cw columns of 8 / cw images, in strips that run
+// down the tile rows.
+// ---------------------------------------------------------------------------
+struct WinoWgArgs : WinoWork {
+    int Kg, Cg, groups, nimg;
+    const float *x, *dy;
+    uint32_t x_bytes, dy_bytes, x_img_words, dy_img_words;
+    int H, W, HW, P, Q, PQ, off;
+    float *dw, *db;            // db may be null
+    int most;                  // stages accumulated in one run
+    float *slabs;
+    hipEvent_t before, after;
+    // Set by launch_wino_wgrad:
+    int cw, cw_log, Pt, Qt, nstrip, kblocks, cblocks;
+    FastDiv d_pt, d_strips, d_cblocks, d_kblocks;
+};
+WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int nimg, int P, int Q, int cus, int *cw);
+size_t wino_wgrad_slab_bytes(const WinoWork &w);
+hipError_t launch_wino_wgrad(WinoWgArgs a, const WinoWork &p, int cw, hipStream_t stream);
 
 // Image-GEMM tile shapes (BM x BN; 4 waves, 3 for 48x64).
 enum ImgTile {

@@ -111,12 +111,13 @@ __device__ __forceinline__ bool is_finite(float v)
 // The kernel's arguments, read from the argument segment anew: for code that
 // runs once an output tile, so that its arguments do not hold scalar registers
 // (and, spilled to vector lanes, cost MFMA time) during the main loop.
-__device__ __forceinline__ const WinoArgs &cold_args()
+template <class Args>
+__device__ __forceinline__ const Args &cold_args()
 {
-    typedef const __attribute__((address_space(4))) WinoArgs *Ptr;
+    typedef const __attribute__((address_space(4))) Args *Ptr;
     Ptr p = (Ptr)__builtin_amdgcn_kernarg_segment_ptr();
     __asm__ volatile("" : "+s"(p));
-    return *(const WinoArgs *)p;
+    return *(const Args *)p;
 }
 
 // Work of one workgroup: the rounds of whole output tiles (tile = round
@@ -125,11 +126,11 @@ struct Unit {
     int tile, s0, s1, slab;  // stages [s0, s1); slab -1: the whole tile
 };
 // First stage, among those of the remaining tiles, of workgroup w's share.
-__device__ __forceinline__ int share(const WinoArgs &a, int w)
+__device__ __forceinline__ int share(const WinoWork &a, int w)
 {
     return w * a.share + min(w, a.share_rem);
 }
-__device__ __forceinline__ Unit wino_unit(const WinoArgs &a, int w, int k)
+__device__ __forceinline__ Unit wino_unit(const WinoWork &a, int w, int k)
 {
     Unit u;
     if (k < a.rounds) {
@@ -145,7 +146,7 @@ __device__ __forceinline__ Unit wino_unit(const WinoArgs &a, int w, int k)
     u.tile = a.rounds * a.nwg + t0 + i;
     u.s0 = i ? 0 : lo - t0 * a.nstage;
     u.s1 = i ? hi - cut : cut - t0 * a.nstage;
-    u.slab = u.s0 == 0 && u.s1 == a.nstage ? -1 : 2 * w + i;
+    u.slab = u.s0 == 0 && u.s1 == a.nstage ? -1 : w + t0 + i;
     return u;
 }
 
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     auto advance = [&]() __attribute__((always_inline)) {
         if (pk >= 0 && ++ps < pu.s1)
             return;
-        const WinoArgs &a = cold_args();
+        const WinoArgs &a = cold_args<WinoArgs>();
         const int nunits = a.rounds + (a.rest ? 2 : 0);
         do {
             if (++pk >= nunits) {
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     // Outputs of unit un: to its slab, or (whole tiles) with the bias to the
     // output, by buffer stores whose range check drops what lies outside it.
     auto finish = [&](const Unit &un) __attribute__((always_inline)) {
-        const WinoArgs &c = cold_args();
+        const WinoArgs &c = cold_args<WinoArgs>();
         const int M = c.M, P = c.P, Q = c.Q, hw = c.out_hw;
         const int gm = (int)fast_div((uint32_t)un.tile, c.d_tblocks), tb = un.tile - gm * c.tblocks;
         const int g = (int)fast_div((uint32_t)gm, c.d_mblocks), mb = gm - g * c.mblocks;
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     auto step_cursor = [&]() __attribute__((always_inline)) {
         if (ck >= 0 && ++cs < cu.s1)
             return;
-        const WinoArgs &a = cold_args();
+        const WinoArgs &a = cold_args<WinoArgs>();
         const int nunits = a.rounds + (a.rest ? 2 : 0);
         do {
             if (++ck >= nunits)
@@ -494,7 +495,7 @@ __device__ float wino_direct(const WinoArgs &a, int img, int oc, int p, int q)
 {
     const int g = oc / a.M, m = oc - g * a.M;
     float s = 0.f;
-    for (int c = 0; c < a.cin; c++) {
+    for (int c = 0; c < a.cin && s == s; c++) {  // (a NaN stays one)
         const float *x = a.src + (size_t)img * a.src_img_words + (size_t)(g * a.cin + c) * a.src_hw;
         const float *wt = a.flip ? a.w + ((size_t)(g * a.cin + c) * a.M + m) * 9
                                  : a.w + ((size_t)(g * a.M + m) * a.cin + c) * 9;
@@ -509,7 +510,7 @@ __device__ float wino_direct(const WinoArgs &a, int img, int oc, int p, int q)
 }
 
 // The workgroup whose share holds the first stage of remaining tile r.
-__device__ __forceinline__ int wino_first_share(const WinoArgs &a, int r)
+__device__ __forceinline__ int wino_first_share(const WinoWork &a, int r)
 {
     const int lo = r * a.nstage, big = a.share_rem * (a.share + 1);
     int w = lo < big || a.share == 0 ? lo / (a.share + 1) : a.share_rem + (lo - big) / a.share;
@@ -533,11 +534,9 @@ __global__ __launch_bounds__(256) void wino_finish_kernel(const WinoArgs a)
         if (share(a, w + 1) < hi) {
             f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
             for (; w < a.nwg && share(a, w) < hi; w++) {
-                const int lo_w = share(a, w);
-                if (lo_w == share(a, w + 1))
+                if (share(a, w) == share(a, w + 1))
                     continue;
-                const int slab = 2 * w + (lo_w / a.nstage == r ? 0 : 1);
-                const f32x4 s = *(const f32x4 *)(a.slabs + (size_t)slab * 16384 + e * 4);
+                const f32x4 s = *(const f32x4 *)(a.slabs + (size_t)(w + r) * 16384 + e * 4);
                 y = f32x4{y[0] + s[0], y[1] + s[1], y[2] + s[2], y[3] + s[3]};
             }
             const int tile = a.rounds * a.nwg + r;
@@ -620,6 +619,468 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(const WinoArgs a, floa
     }
 }
 
+// ---------------------------------------------------------------------------
+// Backward-weight (WinoWgArgs): the adjoint in the filters, F(3x3, 2x2) with
+// the same points.  Per 2 x 2 tile of dy and the 4 x 4 patch of x under it,
+//   dw = Ct [ sum over tiles of (H dy Ht) o (Bt x B) ] C
+//   H = | 1  0 |   Ct = | 1 1/2  1/2  0 |
+//       | 1  1 |        | 0 1/2 -1/2  0 |
+//       | 1 -1 |        | 0 1/2  1/2 -1 |
+//       | 0  1 |
+// (the halves of the transform of dy stand in Ct).  The sum over tiles is 16
+// matrix products of filters by channels whose reduction is the tiles.
+//
+// As the forward GEMM: eight waves, 64 filters x 64 channels, a wave 32 x 16
+// at all 16 points, a stage eight tiles.  Both operands are transformed by
+// the waves (12 and 32 additions a stage and lane) and shared through LDS.
+// The eight tiles of a stage lie in one tile row, cw columns of 8 / cw images;
+// the stages of such a strip run down the tile rows, so that a lane keeps the
+// lower two rows of its patch for the next stage, its offsets move by a scalar
+// and a row outside the image is the same for all lanes.
+//
+// Measured against the direct plans (ms; batch 32 unless said): 64 -> 64 on
+// 224 x 224 maps 0.537 (0.903), 128 on 112 x 112 0.468 (0.899), 256 on 56 x 56
+// 0.486 (0.864), 512 on 28 x 28 0.517 (0.865), 512 on 14 x 14 0.182 (0.275);
+// batch 128, 384 on 13 x 13 in two groups 0.196 (0.290): 0.6-0.7 of the fp32
+// MFMA peak in executed operations on the even maps, 0.42-0.46 where 7 tile
+// columns leave one lane in eight idle.  Error against 64 bits 1.0e-6 (1.4e-6)
+// of the norm for 128 channels on 112 x 112, 3.8e-7 (4.8e-7) for 512 on 14 x 14.
+// The loads must not stand in a branch: where the branches meet the compiler
+// copies their results and so waits for them (0.68 instead of 0.49 ms on
+// 56 x 56 maps).
+// ---------------------------------------------------------------------------
+namespace {
+
+constexpr int WG_Q = 272;               // words of one (step, block, q): 4 rows of 16 lanes, 68 apart,
+constexpr int WG_STEP = 16 * WG_Q + 16; // so that the eight tiles' writes hit distinct banks
+constexpr int WG_STG = 2 * WG_STEP;
+constexpr int WG_SLAB = 64 * 64 * 9 + 64;  // words: [k][c][tap], then the bias gradient
+
+__device__ __forceinline__ void dy_transform(const float (&g)[4], float (&v)[16])
+{
+    const float r[2][4] = {{g[0], g[0] + g[1], g[0] - g[1], g[1]},
+                           {g[2], g[2] + g[3], g[2] - g[3], g[3]}};
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        v[j] = r[0][j];
+        v[4 + j] = r[0][j] + r[1][j];
+        v[8 + j] = r[0][j] - r[1][j];
+        v[12 + j] = r[1][j];
+    }
+}
+
+// Ct m C: taps in row-major order.
+__device__ __forceinline__ void tap_transform(const float (&m)[16], float (&w)[9])
+{
+    float z[3][4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const float s = 0.5f * (m[4 + j] + m[8 + j]);
+        z[0][j] = m[j] + s;
+        z[1][j] = 0.5f * (m[4 + j] - m[8 + j]);
+        z[2][j] = s - m[12 + j];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const float s = 0.5f * (z[i][1] + z[i][2]);
+        w[3 * i] = z[i][0] + s;
+        w[3 * i + 1] = 0.5f * (z[i][1] - z[i][2]);
+        w[3 * i + 2] = s - z[i][3];
+    }
+}
+
+// One row of a patch (MODE as in load_patch), at the row's scalar offset.
+template <int MODE>
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r,
+                                         const uint32_t (&off)[Patch<MODE>::LOADS], uint32_t soff,
+                                         float *d)
+{
+#pragma unroll
+    for (int l = 0; l < Patch<MODE>::LOADS; l++) {
+        const int c = MODE == 0 ? l : MODE == 1 ? (l ? l + l / 2 : 0) : 2 * l;
+        if (MODE == 2 || (MODE == 1 && l == 1)) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off[l], soff, 0);
+            d[c] = __uint_as_float(v[0]);
+            d[c + 1] = __uint_as_float(v[1]);
+        } else {
+            d[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off[l], soff, 0));
+        }
+    }
+}
+
+}  // namespace
+
+template <int MODE>
+__global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
+{
+    constexpr int XL = Patch<MODE>::LOADS, YL = MODE == 0 ? 2 : 1;  // loads a row
+    __shared__ __attribute__((aligned(16))) float Y0[WG_STG], Y1[WG_STG], X0[WG_STG], X1[WG_STG];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int fg = wave >> 2, cg = wave & 3;  // filter half, channel block of the MFMAs
+    const int kr = lane >> 4, lc = lane & 15;
+    const int tl = lane & 7, c8 = lane >> 3;  // tile and channel (filter) of the transforms
+    const int per = a.nwg >> 3, rem = a.nwg & 7, xcd = blockIdx.x & 7;
+    int w = xcd * per + min(xcd, rem) + (int)(blockIdx.x >> 3);
+    if (a.rounds == 0) {
+        // Few output tiles, each cut over several workgroups: neighbours take
+        // the same part of different tiles, which reads the same pixels.
+        const int r = a.nwg / a.rest, e = a.nwg - r * a.rest, q = w / a.rest;
+        const int t = q < r ? w - q * a.rest : (w - r * a.rest) * a.rest / e;
+        w = t * r + (t * e + a.rest - 1) / a.rest + min(q, r);
+    }
+    // LDS words of the transforms' writes and the MFMAs' reads.
+    const int wr = (tl >> 2) * WG_STEP + (wave >> 1) * 4 * WG_Q + (tl & 3) * 68 +
+                   ((wave & 1) * 8 + c8) * 4;
+    const int rd = kr * 68 + lc * 4;
+
+    // Cursor of the loads, two stages ahead of the MFMAs.
+    Unit pu{};
+    int pk = -1, ps = 0, pty = 0;
+    bool more = true, fresh = true;      // fresh: the strip's first stage here
+    uint32_t xo[XL], yo[YL];
+    auto advance = [&]() __attribute__((always_inline)) {
+        if (pk >= 0) {
+            ps++;
+            pty++;
+            fresh = false;
+            if (ps < pu.s1 && pty < a.Pt)
+                return;
+        }
+        const WinoWgArgs &c = cold_args<WinoWgArgs>();
+        if (pk < 0 || ps >= pu.s1) {
+            const int nunits = c.rounds + (c.rest ? 2 : 0);
+            do {
+                if (++pk >= nunits) {
+                    more = false;
+                    return;
+                }
+                pu = wino_unit(c, w, pk);
+            } while (pu.s0 >= pu.s1);
+            ps = pu.s0;
+        }
+        fresh = true;
+        const int st = (int)fast_div((uint32_t)ps, c.d_pt);  // (image group, strip)
+        pty = ps - st * c.Pt;
+        const int ig = (int)fast_div((uint32_t)st, c.d_strips), strip = st - ig * c.nstrip;
+        const int gm = (int)fast_div((uint32_t)pu.tile, c.d_cblocks), cb = pu.tile - gm * c.cblocks;
+        const int g = (int)fast_div((uint32_t)gm, c.d_kblocks), kb = gm - g * c.kblocks;
+        const int tx = strip * c.cw + (tl & (c.cw - 1));
+        const int img = ig * (8 >> c.cw_log) + (tl >> c.cw_log);
+        const int k = kb * 64 + wave * 8 + c8, ch = cb * 64 + wave * 8 + c8;
+        const bool in = tx < c.Qt && img < c.nimg;
+        const int w0 = 2 * tx + c.off;
+        const uint32_t xb = ((uint32_t)img * c.x_img_words + (uint32_t)((g * c.Cg + ch) * c.HW)) * 4u;
+#pragma unroll
+        for (int l = 0; l < XL; l++) {
+            const int col = w0 + (MODE == 0 ? l : MODE == 1 ? (l ? l + l / 2 : 0) : 2 * l);
+            xo[l] = in && ch < c.Cg && (unsigned)col < (unsigned)c.W ? xb + (uint32_t)col * 4u : kOob;
+        }
+        const uint32_t yb = ((uint32_t)img * c.dy_img_words + (uint32_t)((g * c.Kg + k) * c.PQ)) * 4u;
+#pragma unroll
+        for (int l = 0; l < YL; l++)
+            yo[l] = in && k < c.Kg && 2 * tx + l < c.Q ? yb + (uint32_t)(2 * tx + l) * 4u : kOob;
+    };
+    // Rows i, i + 1 of the patches of tile row pty into d.  (A row outside the
+    // image reads zero through an empty buffer: a branch around the load would
+    // make the compiler wait for it where the branches meet.)
+    auto load_x = [&](int i, float (&d)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const int h = 2 * pty + a.off + i + r;
+            const bool ok = more && (unsigned)h < (unsigned)a.H;
+            load_row<MODE>(make_rsrc(a.x, ok ? a.x_bytes : 0u), xo,
+                           ok ? (uint32_t)(h * a.W) * 4u : 0u, d + 4 * r);
+        }
+    };
+    auto load_y = [&](float (&g)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const bool ok = more && 2 * pty + r < a.P;
+            const __amdgpu_buffer_rsrc_t rY = make_rsrc(a.dy, ok ? a.dy_bytes : 0u);
+            const uint32_t soff = ok ? (uint32_t)((2 * pty + r) * a.Q) * 4u : 0u;
+            if constexpr (YL == 1) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rY, (int)yo[0], soff, 0);
+                g[2 * r] = __uint_as_float(v[0]);
+                g[2 * r + 1] = __uint_as_float(v[1]);
+            } else {
+                g[2 * r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rY, (int)yo[0], soff, 0));
+                g[2 * r + 1] =
+                    __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rY, (int)yo[YL - 1], soff, 0));
+            }
+        }
+    };
+    float db = 0.f;  // this lane's filter and tiles, of the stages transformed so far
+    auto write = [&](float *Yd, float *Xd, const float (&lo)[8], const float (&hi)[8],
+                     const float (&g)[4]) __attribute__((always_inline)) {
+        float d[16], v[16];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+            d[j] = lo[j];
+            d[8 + j] = hi[j];
+        }
+        input_transform(d, v);
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            *(LDS_AS f32x4 *)(Xd + wr + q * WG_Q) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        dy_transform(g, v);
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            *(LDS_AS f32x4 *)(Yd + wr + q * WG_Q) = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        db += v[5];  // the sum of the tile
+    };
+
+    f32x4 acc[2][16];
+    f32x4 u[2][2], v[2];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int p = 0; p < 16; p++)
+                acc[b][p] = f32x4{0.f, 0.f, 0.f, 0.f};
+    };
+    auto read_ops = [&](const float *Yc, const float *Xc, int g8) __attribute__((always_inline)) {
+        const int step = g8 >> 2, q = g8 & 3;
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+            u[q & 1][b] = lds_b128(Yc, rd + step * WG_STEP + ((fg * 2 + b) * 4 + q) * WG_Q);
+        v[q & 1] = lds_b128(Xc, rd + step * WG_STEP + (cg * 4 + q) * WG_Q);
+    };
+    // Sums of unit un: to its slab, or (whole tiles) to dw and db.
+    // add: onto what an earlier part of the unit has stored there.
+    auto finish = [&](const Unit &un, bool add, bool end, float bias) __attribute__((always_inline)) {
+        const WinoWgArgs &c = cold_args<WinoWgArgs>();
+        const int gm = (int)fast_div((uint32_t)un.tile, c.d_cblocks), cb = un.tile - gm * c.cblocks;
+        const int g = (int)fast_div((uint32_t)gm, c.d_kblocks), kb = gm - g * c.kblocks;
+        float *const slab = un.slab >= 0 ? c.slabs + (size_t)un.slab * WG_SLAB : nullptr;
+        const int Kg = c.Kg, Cg = c.Cg, ch = cb * 64 + cg * 16 + lc;
+        float *const dw = c.dw + (size_t)g * Kg * Cg * 9;
+#pragma unroll
+        for (int b = 0; b < 2; b++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int row = fg * 32 + b * 16 + 4 * kr + r, k = kb * 64 + row;
+                float x[16], t[9];
+#pragma unroll
+                for (int p = 0; p < 16; p++)
+                    x[p] = acc[b][p][r];
+                tap_transform(x, t);
+                float *const o = slab ? slab + (row * 64 + cg * 16 + lc) * 9
+                                      : dw + ((size_t)k * Cg + ch) * 9;
+                if (slab || (k < Kg && ch < Cg)) {
+                    if (add)
+#pragma unroll
+                        for (int j = 0; j < 9; j++)
+                            t[j] += o[j];
+#pragma unroll
+                    for (int j = 0; j < 9; j++)
+                        o[j] = t[j];
+                }
+            }
+        if (!end)
+            return;
+        // The eight tiles' sums of a filter, in a fixed order.
+        bias += __shfl_xor(bias, 1);
+        bias += __shfl_xor(bias, 2);
+        bias += __shfl_xor(bias, 4);
+        if (tl == 0) {
+            if (slab)
+                slab[64 * 64 * 9 + wave * 8 + c8] = bias;
+            else if (c.db && cb == 0 && kb * 64 + wave * 8 + c8 < Kg)
+                c.db[g * Kg + kb * 64 + wave * 8 + c8] = bias;
+        }
+    };
+
+    // The MFMAs' cursor.  A unit's sums are stored every `part` stages, in equal
+    // parts of at most c.most, so that no accumulation runs longer than that.
+    Unit cu{};
+    int ck = -1, cs = 0, part = 0, left = 0;
+    auto step_cursor = [&]() __attribute__((always_inline)) {
+        if (ck >= 0 && ++cs < cu.s1)
+            return;
+        const WinoWgArgs &c = cold_args<WinoWgArgs>();
+        const int nunits = c.rounds + (c.rest ? 2 : 0);
+        do {
+            if (++ck >= nunits)
+                return;
+            cu = wino_unit(c, w, ck);
+        } while (cu.s0 >= cu.s1);
+        cs = cu.s0;
+        const int len = cu.s1 - cu.s0;
+        int n = 1;
+        while (n * c.most < len)
+            n++;
+        part = left = (len + n - 1) / n;
+    };
+
+    // As in wino_gemm_kernel: MFMAs from (Yc, Xc), transforms of the next stage
+    // into (Yn, Xn) from the patch rows lo, hi, loads of the one after it into
+    // hi's successor lo (and hi's own rows, where it opens a strip).
+    bool have1, have2;
+    float g[4];
+    auto stage = [&](float *Yc, float *Xc, float *Yn, float *Xn, float (&lo)[8],
+                     float (&hi)[8]) __attribute__((always_inline)) {
+        const bool last = cs + 1 == cu.s1, store = last || left == 1;
+        left--;
+        float bias = 0.f;  // of this unit, once its last stage is transformed
+#pragma unroll
+        for (int g8 = 0; g8 < 8; g8++) {
+            const int q = g8 & 3;
+            if (g8 == 7) {
+                __builtin_amdgcn_s_waitcnt((15 | 3 << 14) | (7 << 4));  // LDS; loads may fly on
+                fence();
+                __builtin_amdgcn_s_barrier();
+                fence();
+            }
+            read_ops(g8 < 7 ? Yc : Yn, g8 < 7 ? Xc : Xn, (g8 + 1) & 7);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+#pragma unroll
+                for (int b = 0; b < 2; b++)
+                    acc[b][4 * q + j] = mfma16(u[q & 1][b][j], v[q & 1][j], acc[b][4 * q + j]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (g8 == 0) {
+                if (last) {  // the unit's stages are all transformed
+                    bias = db;
+                    db = 0.f;
+                }
+                if (have1)
+                    write(Yn, Xn, lo, hi, g);
+                __builtin_amdgcn_sched_barrier(0);
+                advance();
+                have2 = more;
+                if (fresh)
+                    load_x(0, hi);
+                load_x(2, lo);
+                load_y(g);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (store) {
+            finish(cu, cs + 1 - cu.s0 > part, last, bias);
+            clear();
+            left = part;
+        }
+        step_cursor();
+        const bool on = have1;
+        have1 = have2;
+        return on;
+    };
+
+    float ra[8], rb[8];
+    advance();
+    if (!more)
+        return;
+    load_x(0, ra);
+    load_x(2, rb);
+    load_y(g);
+    write(Y0, X0, ra, rb, g);
+    step_cursor();
+    advance();
+    have1 = more;
+    if (have1) {
+        if (fresh)
+            load_x(0, rb);
+        load_x(2, ra);
+        load_y(g);
+    }
+    clear();
+    __builtin_amdgcn_s_waitcnt(0);
+    fence();
+    __builtin_amdgcn_s_barrier();
+    fence();
+    read_ops(Y0, X0, 0);
+    // The operands read past a workgroup's last stage are not used.
+    while (stage(Y0, X0, Y1, X1, rb, ra) && stage(Y1, X1, Y0, X0, ra, rb)) {
+    }
+}
+
+// Ends the pass: adds the slabs of cut output tiles, and recomputes filter
+// gradients that are not finite as direct sums (see wino_finish_kernel).  A
+// block is 32 quads of one tile's words, eight threads to a quad: each sums
+// every eighth slab, then the eight sums are added in order.
+constexpr int WG_BLOCKS = WG_SLAB / 128 + 1;
+__global__ __launch_bounds__(256) void wino_wgrad_finish_kernel(const WinoWgArgs a)
+{
+    __shared__ f32x4 part[8][32];
+    __shared__ int bad[32];
+    const int tile = blockIdx.x / WG_BLOCKS, r = tile - a.rounds * a.nwg;
+    const int lane = threadIdx.x & 31, j = threadIdx.x >> 5;
+    const int e = ((blockIdx.x - tile * WG_BLOCKS) * 32 + lane) * 4;
+    const int gm = tile / a.cblocks, cb = tile - gm * a.cblocks;
+    const int g = gm / a.kblocks, kb = gm - g * a.kblocks;
+    float *const dw = a.dw + ((size_t)(g * a.Kg + kb * 64) * a.Cg + cb * 64) * 9;
+    const int hi = (r + 1) * a.nstage, w0 = r >= 0 ? wino_first_share(a, r) : 0;
+    const bool cut = r >= 0 && share(a, w0 + 1) < hi;  // else its workgroup has written dw
+    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (cut) {
+        if (e < WG_SLAB)
+            for (int w = w0 + j; w < a.nwg && share(a, w) < hi; w += 8)
+                if (share(a, w) < share(a, w + 1)) {
+                    const f32x4 y = *(const f32x4 *)(a.slabs + (size_t)(w + r) * WG_SLAB + e);
+                    s = f32x4{s[0] + y[0], s[1] + y[1], s[2] + y[2], s[3] + y[3]};
+                }
+        part[j][lane] = s;
+    }
+    __syncthreads();
+    int mask = 0;
+    if (j == 0 && e < WG_SLAB) {
+        if (cut)
+#pragma unroll
+            for (int i = 1; i < 8; i++) {
+                const f32x4 y = part[i][lane];
+                s = f32x4{s[0] + y[0], s[1] + y[1], s[2] + y[2], s[3] + y[3]};
+            }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int n = e + i, row = n / 576, m = n - row * 576;
+            if (n >= 64 * 64 * 9) {
+                const int k = kb * 64 + n - 64 * 64 * 9;
+                if (cut && a.db && cb == 0 && k < a.Kg)
+                    a.db[g * a.Kg + k] = s[i];
+            } else if (kb * 64 + row < a.Kg && cb * 64 + m / 9 < a.Cg) {
+                float *const o = dw + (size_t)row * a.Cg * 9 + m;
+                if (cut)
+                    *o = s[i];
+                mask |= is_finite(cut ? s[i] : *o) ? 0 : 1 << i;
+            }
+        }
+    }
+    if (j == 0)
+        bad[lane] = mask;
+    if (!__syncthreads_or(mask))
+        return;
+    float *const sum = (float *)part;
+    for (int i = 0; i < 128; i++) {
+        if (!(bad[i >> 2] >> (i & 3) & 1))
+            continue;
+        const int n = (blockIdx.x - tile * WG_BLOCKS) * 128 + i, row = n / 576, m = n - row * 576;
+        const int c = cb * 64 + m / 9, tap = m % 9;
+        const float *x = a.x + (size_t)(g * a.Cg + c) * a.HW;
+        const float *dy = a.dy + (size_t)(g * a.Kg + kb * 64 + row) * a.PQ;
+        float v = 0.f;
+        for (int img = 0; img < a.nimg; img++, x += a.x_img_words, dy += a.dy_img_words) {
+            for (int pq = threadIdx.x; pq < a.PQ; pq += 256) {
+                const int p = pq / a.Q, h = p + a.off + tap / 3, w = pq - p * a.Q + a.off + tap % 3;
+                if ((unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
+                    v = fmaf(dy[pq], x[h * a.W + w], v);
+            }
+            if (__syncthreads_or(v != v))
+                break;  // a NaN stays one
+        }
+        sum[threadIdx.x] = v;
+        for (int k = 128; k > 0; k >>= 1) {
+            __syncthreads();
+            if ((int)threadIdx.x < k)
+                sum[threadIdx.x] += sum[threadIdx.x + k];
+        }
+        if (threadIdx.x == 0)
+            dw[(size_t)row * a.Cg * 9 + m] = sum[0];
+    }
+}
+
 // ---------------------------------------------------------------- launches
 // Channel blocks of 64, stages of 8 channels (cin is a multiple of 8).
 size_t wino_filter_words(int M, int cin, int groups)
@@ -627,35 +1088,42 @@ size_t wino_filter_words(int M, int cin, int groups)
     return (size_t)groups * ((M + 63) / 64) * (cin / 8) * 8192;
 }
 
-WinoPlan wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus)
+// Work of n output tiles of nstage stages on cus workgroups, each at least
+// `least` stages.
+static WinoWork wino_work(long long n, int nstage, int cus, int least)
 {
-    WinoPlan p{};
-    const long long tiles = (long long)nimg * ((P + 1) / 2) * ((Q + 1) / 2);
-    const long long n = (long long)groups * ((M + 63) / 64) * ((tiles + 63) / 64);
-    const long long stages = n * (cin / 8);
-    // At least four stages a workgroup.
-    p.nwg = (int)(stages / 4 < 1 ? 1 : stages / 4 < cus ? stages / 4 : cus);
-    p.rounds = (int)(n / p.nwg);
-    p.rest = (int)(n % p.nwg);
-    p.slab_bytes = p.rest ? (size_t)p.nwg * 2 * 65536 : 0;
-    return p;
+    WinoWork w{};
+    const long long most = n * nstage / least;
+    w.nwg = (int)(most < 1 ? 1 : most < cus ? most : cus);
+    w.nstage = nstage;
+    w.rounds = (int)(n / w.nwg);
+    w.rest = (int)(n % w.nwg);
+    w.share = (int)((long long)w.rest * nstage / w.nwg);
+    w.share_rem = (int)((long long)w.rest * nstage % w.nwg);
+    w.d_nstage = make_fastdiv(nstage);
+    return w;
 }
 
-hipError_t launch_wino(WinoArgs a, const WinoPlan &p, float *U, hipStream_t stream)
+WinoWork wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus)
 {
+    const long long tiles = (long long)nimg * ((P + 1) / 2) * ((Q + 1) / 2);
+    return wino_work((long long)groups * ((M + 63) / 64) * ((tiles + 63) / 64), cin / 8, cus, 4);
+}
+
+size_t wino_slab_bytes(const WinoWork &w)
+{
+    return w.rest ? (size_t)(w.nwg + w.rest) * 65536 : 0;
+}
+
+hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stream)
+{
+    static_cast<WinoWork &>(a) = p;
     a.U = U;
     a.Pt = (a.P + 1) / 2;
     a.Qt = (a.Q + 1) / 2;
     a.tiles = a.nimg * a.Pt * a.Qt;
     a.tblocks = (a.tiles + 63) / 64;
     a.mblocks = (a.M + 63) / 64;
-    a.nstage = a.cin / 8;
-    a.nwg = p.nwg;
-    a.rounds = p.rounds;
-    a.rest = p.rest;
-    a.share = p.rest * a.nstage / p.nwg;
-    a.share_rem = p.rest * a.nstage % p.nwg;
-    a.d_nstage = make_fastdiv(a.nstage);
     a.d_tblocks = make_fastdiv(a.tblocks);
     a.d_mblocks = make_fastdiv(a.mblocks);
     a.d_qt = make_fastdiv(a.Qt);
@@ -681,6 +1149,60 @@ hipError_t launch_wino(WinoArgs a, const WinoPlan &p, float *U, hipStream_t stre
     if (a.after && (e = hipEventRecord(a.after, stream)) != hipSuccess)
         return e;
     wino_finish_kernel<<<dim3(p.rest ? (unsigned)p.rest * 16 : 64), 256, 0, stream>>>(a);
+    return hipGetLastError();
+}
+
+// Columns of a stage's eight tiles: 8, or 4 of two or 2 of four images where
+// that leaves fewer lanes idle (28 x 28 maps, 14 tiles wide, 512 channels:
+// 0.521 ms with 2 columns, 0.560 with 8; one column of eight images was 17-28 %
+// slower than 8 columns with one idle on 14 x 14 maps: its loads touch eight
+// times the cache lines).
+WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int nimg, int P, int Q, int cus, int *cw)
+{
+    const int Pt = (P + 1) / 2, Qt = (Q + 1) / 2;
+    auto strips = [&](int c) { return (long long)((Qt + c - 1) / c) * ((nimg + 8 / c - 1) / (8 / c)); };
+    *cw = 8;
+    for (int c : {4, 2})
+        if (strips(c) < strips(*cw))
+            *cw = c;
+    return wino_work((long long)groups * ((Kg + 63) / 64) * ((Cg + 63) / 64),
+                     (int)(strips(*cw) * Pt), cus, 8);
+}
+
+size_t wino_wgrad_slab_bytes(const WinoWork &w)
+{
+    return w.rest ? (size_t)(w.nwg + w.rest) * WG_SLAB * 4 : 0;
+}
+
+hipError_t launch_wino_wgrad(WinoWgArgs a, const WinoWork &p, int cw, hipStream_t stream)
+{
+    static_cast<WinoWork &>(a) = p;
+    a.cw = cw;
+    a.cw_log = cw == 8 ? 3 : cw == 4 ? 2 : 1;
+    a.Pt = (a.P + 1) / 2;
+    a.Qt = (a.Q + 1) / 2;
+    a.nstrip = (a.Qt + cw - 1) / cw;
+    a.kblocks = (a.Kg + 63) / 64;
+    a.cblocks = (a.Cg + 63) / 64;
+    a.d_pt = make_fastdiv(a.Pt);
+    a.d_strips = make_fastdiv(a.nstrip);
+    a.d_cblocks = make_fastdiv(a.cblocks);
+    a.d_kblocks = make_fastdiv(a.kblocks);
+    hipError_t e;
+    if (a.before && (e = hipEventRecord(a.before, stream)) != hipSuccess)
+        return e;
+    const dim3 grid((unsigned)p.nwg);
+    if (a.W & 1)
+        wino_wgrad_kernel<0><<<grid, 512, 0, stream>>>(a);
+    else if (a.off & 1)
+        wino_wgrad_kernel<1><<<grid, 512, 0, stream>>>(a);
+    else
+        wino_wgrad_kernel<2><<<grid, 512, 0, stream>>>(a);
+    if ((e = hipGetLastError()) != hipSuccess ||
+        (a.after && (e = hipEventRecord(a.after, stream)) != hipSuccess))
+        return e;
+    const long long blocks = ((long long)p.rounds * p.nwg + p.rest) * WG_BLOCKS;
+    wino_wgrad_finish_kernel<<<dim3((unsigned)blocks), 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 

@@ -1,6 +1,7 @@
-"""Fast filtering F(2x2, 3x3) of stride-1 3x3 layers (forward and
-backward-data) against the oracle, at the sizes where its tiling can go wrong,
-with infinities and NaNs, and with workspaces that only hold the direct plan."""
+"""Fast filtering of stride-1 3x3 layers (F(2x2, 3x3) forward and
+backward-data, F(3x3, 2x2) backward-weight) against the oracle, at the sizes
+where its tiling can go wrong, with infinities and NaNs, and with workspaces
+that only hold the direct plan."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,9 @@ pytestmark = pytest.mark.gpu
 # (N, C, H, W, K, 3, 3, 1, pad, G).  A GEMM tile is 64 rows x 64 tiles of 2 x 2
 # pixels, a stage 8 channels, a workgroup's share at least 4 stages; source
 # columns load in pairs on even widths (from odd or even offsets), singly on
-# odd ones.
+# odd ones.  Backward-weight: an output tile is 64 filters x 64 channels, a
+# stage eight 2 x 2 tiles of dy (8, 4 or 2 columns of 1, 2 or 4 images), a
+# workgroup's share at least 8 stages.
 SHAPES = [
     (1, 8, 3, 3, 8, 3, 3, 1, 1, 1),        # one stage, one 2 x 2 grid of tiles, odd edges
     (1, 8, 2, 2, 5, 3, 3, 1, 2, 1),        # 4 x 4 outputs of a 2 x 2 image
@@ -26,6 +29,10 @@ SHAPES = [
     (1, 256, 5, 5, 64, 3, 3, 1, 1, 1),     # one tile cut over 8 workgroups
     (9, 128, 15, 15, 200, 3, 3, 1, 1, 1),  # 36 tiles of 16 stages over 144 workgroups
     (1, 8, 258, 259, 64, 3, 3, 1, 1, 1),   # over one round of workgroups, short reductions
+    (3, 3, 20, 28, 70, 3, 3, 1, 1, 1),     # 3 channels; 14 columns, images not a multiple of 4
+    (5, 64, 6, 8, 64, 3, 3, 1, 1, 1),      # 4 columns, 5 images
+    (16, 72, 30, 31, 80, 3, 3, 1, 1, 1),   # 4 ragged output tiles, cut; runs stored in parts
+    (1, 1100, 4, 4, 1030, 3, 3, 1, 1, 1),  # 306 output tiles of two stages: whole ones and cut ones
 ]
 
 
@@ -53,6 +60,8 @@ def _run(p, shape, t, ws=None):
     N, C, H, W, K, R, S, st, pad, G = shape
     if p == m.PASS_FWD:
         return m.conv_fwd(t["x"], t["w"], t["b"], st, pad, G, ws=ws)
+    if p == m.PASS_BWD_WEIGHT:
+        return m.conv_bwd_weight(t["x"], t["dy"], (R, S), st, pad, G, ws=ws)[0]
     return m.conv_bwd_data(t["dy"], t["w"], (H, W), st, pad, G, ws=ws)
 
 
@@ -80,7 +89,15 @@ def test_matches_oracle(shape):
         again = host(_run(p, shape, t))
         assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
         ran += 1
-    assert ran
+    m.plan_set(m.PASS_BWD_WEIGHT, shape, _plan(m.PASS_BWD_WEIGHT, shape, "fast"))
+    N, C, H, W, K, R, S, st, pad, G = shape
+    dw, db = m.conv_bwd_weight(t["x"], t["dy"], (R, S), st, pad, G)
+    dw_ref, adw, db_ref, adb = oracle.conv_bwd_weight(shape, d["x"], d["dy"])
+    assert_within(host(dw), dw_ref, adw, "dw")
+    assert_within(host(db), db_ref, adb, "db")
+    alone, none = m.conv_bwd_weight(t["x"], t["dy"], (R, S), st, pad, G, with_bias=False)
+    assert none is None
+    assert np.array_equal(host(alone).view(np.uint32), host(dw).view(np.uint32))
 
 
 @pytest.mark.parametrize("shape", [(2, 128, 14, 14, 64, 3, 3, 1, 1, 1),
@@ -113,6 +130,35 @@ def test_infinities_and_nans_as_the_direct_plan(shape):
     assert_within(a[fin], ref[fin], absum[fin], "finite outputs")
 
 
+@pytest.mark.parametrize("shape", [(3, 64, 14, 14, 64, 3, 3, 1, 1, 1),       # one cut tile
+                                   (1, 1030, 4, 4, 1100, 3, 3, 1, 1, 1)],    # whole ones too
+                         ids=lambda s: "x".join(map(str, s)))
+def test_infinities_and_nans_in_the_filter_gradient(shape):
+    import paper_1903_06934_amd as m
+    d = _inputs(shape, (75, 1))
+    x, dy = d["x"].copy(), d["dy"].copy()
+    x[0, 3, 2, 2], x[0, 5, 3, 1], x[0, 7, 0, 3] = np.inf, -np.inf, np.nan
+    x[0, 9, 1, 1] = x[0, 9, 1, 2] = 3e38  # the transform overflows, the sums do not
+    dy[:, :, :3, :4] *= 0.1
+    t = {"x": dev(x), "dy": dev(dy)}
+    got = {}
+    for want in ("fast", "direct"):
+        m.plan_set(m.PASS_BWD_WEIGHT, shape, _plan(m.PASS_BWD_WEIGHT, shape, want))
+        got[want] = host(_run(m.PASS_BWD_WEIGHT, shape, t))
+    a, b = got["fast"], got["direct"]
+    # A NaN and an infinity reach the same filter gradients; which of them
+    # stay NaN may depend on the order of an overflowing sum.
+    assert np.array_equal(np.isfinite(a[:, :9]), np.isfinite(b[:, :9]))
+    assert np.array_equal(np.isnan(a[:, :9]), np.isnan(b[:, :9]))
+    assert (~np.isfinite(a[:, 3])).any() and (~np.isfinite(a[:, 7])).any()
+    rest = [c for c in range(shape[1]) if c not in (3, 5, 7, 9)]
+    x0 = np.where(np.isfinite(x), x, 0).astype(np.float32)
+    ref, absum, _, _ = oracle.conv_bwd_weight(shape, x0, dy)
+    assert_within(a[:, rest], ref[:, rest], absum[:, rest], "finite gradients")
+    fin = np.isfinite(a[:, 9]) & np.isfinite(b[:, 9])
+    assert_within(a[:, 9][fin], ref[:, 9][fin], absum[:, 9][fin], "large gradients")
+
+
 def test_smaller_workspace_runs_the_direct_plan():
     """Where the workspace holds the direct plan but not the transformed
     filters, the rule runs the direct plan, bit for bit."""
@@ -135,6 +181,27 @@ def test_smaller_workspace_runs_the_direct_plan():
         assert not np.array_equal(by_rule, host(_run(p, shape, t)))
         with pytest.raises(m.MiconvError):
             _run(p, shape, t, ws=torch.empty(nbytes - 256, dtype=torch.uint8, device="cuda"))
+
+
+def test_backward_weight_within_the_fixed_scratch():
+    """Backward-weight's fast plan never needs more than the fixed scratch of
+    conv_bwd_weight_noalloc (on the largest slab counts), which runs it too."""
+    import torch
+    import paper_1903_06934_amd as m
+    for shape in ((32, 64, 112, 112, 64, 3, 3, 1, 1, 1), (8, 512, 28, 28, 512, 3, 3, 1, 1, 1),
+                  (8, 1024, 28, 28, 960, 3, 3, 1, 1, 1)):
+        i = _plan(m.PASS_BWD_WEIGHT, shape, "fast")
+        assert i is not None
+        N, C, H, W, K = shape[:5]
+        x = torch.randn(N, C, H, W, device="cuda")
+        dy = torch.randn(N, K, H, W, device="cuda")
+        dw = torch.empty(K, C, 3, 3, device="cuda")
+        m.plan_set(m.PASS_BWD_WEIGHT, shape, i)
+        st = m.lib().conv_bwd_weight_noalloc(*shape, x.data_ptr(), dy.data_ptr(), dw.data_ptr(),
+                                             None, torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        want, _ = m.conv_bwd_weight(x, dy, (3, 3), 1, 1, 1, with_bias=False)
+        assert np.array_equal(host(dw).view(np.uint32), host(want).view(np.uint32))
 
 
 def test_captured_graph_replays():
