@@ -187,18 +187,19 @@ int conv_set_timing_events(hipEvent_t before, hipEvent_t after);
  * the conv_* calls consult; the table is thread-safe.  Arguments after
  * `pass` are those of the pass.
  *
- * Fast filtering.  Stride-1 3 x 3 layers may also run by minimal filtering
- * (F(2x2, 3x3): 16 multiplications instead of 36 for 2 x 2 outputs and a
- * channel, in fp32 throughout; backward-weight F(3x3, 2x2)), whose results differ from a direct sum's by
+ * Fast filtering.  Stride-1 3 x 3 and 5 x 5 layers may also run by minimal
+ * filtering (F(2x2, 3x3), backward-weight F(3x3, 2x2), 5 x 5 filters in four
+ * 3 x 3 parts: 16 multiplications instead of 36, or 64 instead of 100, for
+ * 2 x 2 outputs and a channel), in fp32 throughout.  Its results differ by
  * rounding only: less than a direct plan's on dense data; where a layer's
  * filters or inputs cancel or skip products exactly (a filter with a single
  * tap, say), by roundings of the size of the neighbouring products.  Outputs
- * that are infinite or NaN are recomputed as direct sums.  The rule uses it
- * where it measured faster, and candidate 0 then stands for it; its name is
- * that of the rule's direct plan, which the call runs when the workspace only
- * holds that one (conv_plan_workspace_size gives the need of the faster), and
- * which the list offers once more, named "..., products summed directly".
- * Where the rule does not use it the list offers it as "fast filtering ...".
+ * that are infinite or NaN are recomputed as direct sums.  Where it applies
+ * the list offers it as "fast filtering ...".  The rule uses it where it
+ * measured faster and the workspace holds it (conv_workspace_size always does);
+ * candidate 0 keeps the name and the workspace of the rule's direct plan, which
+ * runs when the workspace only holds that one, and which the list then offers
+ * once more, named "..., products summed directly".
  *
  * conv_plan_count:  number of candidates (>= 1), or a negative status
  *                   (MICONV_ERR_SHAPE, MICONV_ERR_PASS).  Host-only.

@@ -553,12 +553,13 @@ bool halo_rule(int M, int cin, int nimg, int Pout, int Qout, int src_w, int R, i
 }
 
 // ------------------------------------------------------------ fast filtering
-// Stride-1 3 x 3 layers by F(2x2, 3x3) (wino_kernels.hip): M rows over cin
+// Stride-1 3 x 3 layers, and 5 x 5 ones in four 3 x 3 parts, by F(2x2, 3x3)
+// (wino_kernels.hip): M rows over cin
 // source channels per group, all images in one launch.
 bool wino_applies(const Geom &g, int M, int cin)
 {
-    return g.R == 3 && g.S == 3 && g.st == 1 && cin % 8 == 0 && images_per_launch(g) >= g.N &&
-           (long long)wino_filter_words(M, cin, g.G) <= kMaxChunkElems;
+    return halo_filter(g) && cin % 8 == 0 && images_per_launch(g) >= g.N &&
+           (long long)wino_filter_words(M, cin, g.G, g.R) <= kMaxChunkElems;
 }
 
 // The built-in rule's use of it.  Its GEMM runs in stages (64 rows x 64 tiles
@@ -574,38 +575,48 @@ bool wino_applies(const Geom &g, int M, int cin)
 // 1.4-1.5.  Fewer than 32 rows leave most of a 64-row tile idle; with fewer
 // than 32 channels the transforms' rounding is no longer small beside the
 // sums' (error against 64 bits at 16 channels: equal to the direct plans').
+// 5 x 5 layers (16 multiplications of 25, so less to gain) take it from 64
+// channels and 48 rows on, or 48 channels and 12 stages a CU: AlexNet conv2 (48
+// to 128 channels a group, 27 x 27, batch 128) 1.20 forward, 1.25 backward-data;
+// 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.2-1.9; 48 to 128 on 14 x 14
+// (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.
 bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout)
 {
     if (cin < 32 || M < 32 || !wino_applies(g, M, cin))
         return false;
+    const long long tiles = (long long)g.N * ((Pout + 1) / 2) * ((Qout + 1) / 2);
+    if (g.R == 5)
+        return M >= 48 && cin >= 48 &&
+               (cin >= 64 || (long long)g.G * ((M + 63) / 64) * ((tiles + 63) / 64) * (cin / 2) >=
+                                 12 * num_cus());
     if (cin >= 128 && M >= 64)
         return true;
-    const long long tiles = (long long)g.N * ((Pout + 1) / 2) * ((Qout + 1) / 2);
     return (long long)g.G * ((M + 63) / 64) * ((tiles + 63) / 64) * (cin / 8) >= 6 * num_cus();
 }
 
 // The flag, the transformed filters, the slabs of cut tiles.
 size_t wino_ws(const Geom &g, int M, int cin, int Pout, int Qout)
 {
-    return kAlign + align_up(wino_filter_words(M, cin, g.G) * sizeof(float)) +
-           wino_slab_bytes(wino_plan(M, cin, g.G, g.N, Pout, Qout, num_cus()));
+    return kAlign + align_up(wino_filter_words(M, cin, g.G, g.R) * sizeof(float)) +
+           wino_slab_bytes(wino_plan(M, cin, g.G, g.R, g.N, Pout, Qout, num_cus()));
 }
 
-// Candidates after the direct ones: fast filtering where the rule does not
-// take it already, else the rule's direct plan.
+// Candidates after the direct ones: fast filtering, and where the rule uses it
+// the rule's direct plan.
 template <class P, class Make>
-void wino_variants(const ImgPlan &rule, bool applies, Make make, std::vector<P> &out)
+void wino_variants(ImgPlan rule, bool applies, Make make, std::vector<P> &out)
 {
+    if (applies) {
+        ImgPlan f{};
+        f.nsplit = 1;
+        f.wino = WINO_PLAN;
+        out.push_back(make(f));
+    }
     if (rule.wino == WINO_RULE) {
         ImgPlan d = rule;
         d.wino = 0;
         d.plain = true;
         out.push_back(make(d));
-    } else if (applies) {
-        ImgPlan f{};
-        f.nsplit = 1;
-        f.wino = WINO_PLAN;
-        out.push_back(make(f));
     }
 }
 
@@ -1269,18 +1280,18 @@ WgradPlan wgrad_halo_plan(const Geom &g, int tw, int scale = 0, int ct = 1, int 
     return p;
 }
 
-// Fast filtering of backward-weight (wino_wgrad_kernel): stride-1 3 x 3 layers,
+// Fast filtering of backward-weight (wino_wgrad_kernel): the same layers,
 // any channel counts, all images in one launch.
 bool wgrad_wino_applies(const Geom &g)
 {
-    return g.R == 3 && g.S == 3 && g.st == 1 && images_per_launch(g) >= g.N;
+    return halo_filter(g) && images_per_launch(g) >= g.N;
 }
 
 size_t wgrad_wino_ws(const Geom &g)
 {
     int cw;
     return align_up(wino_wgrad_slab_bytes(
-        wino_wgrad_plan(g.Kg, g.Cg, g.G, g.N, g.P, g.Q, num_cus(), &cw)));
+        wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, g.N, g.P, g.Q, num_cus(), &cw)));
 }
 
 // The built-in rule's use of it: where its 64 x 64 tiles are mostly real, a tile
@@ -1290,16 +1301,22 @@ size_t wgrad_wino_ws(const Geom &g)
 // layers at batch 64 1.2-1.5; AlexNet conv3-conv5 1.4-1.5; 64 to 256 channels
 // at batch 16 1.06-1.16 (1568 stages); 512 channels on 14 x 14 maps 0.84 at
 // batch 4 (24 stages a tile), 1.27 at batch 16; half-empty tiles (32 -> 64
-// channels) 0.93-1.0, 16 -> 16 0.6-0.8.
+// channels) 0.93-1.0, 16 -> 16 0.6-0.8.  5 x 5 layers on maps of an even width
+// with at least 16 stages a CU (the four parts of the filter count as tiles):
+// 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.24-1.5; AlexNet conv2 (27 x 27)
+// 0.89, 96 -> 128 on 8 x 8 (8 stages a CU) 0.91.
 bool wgrad_wino_rule(const Geom &g)
 {
     if (!wgrad_wino_applies(g))
         return false;
     int cw;
-    const WinoWork w = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.N, g.P, g.Q, num_cus(), &cw);
+    const WinoWork w = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, g.N, g.P, g.Q, num_cus(), &cw);
     const long long kb = (g.Kg + 63) / 64, cb = (g.Cg + 63) / 64;
-    return 10LL * g.Kg * g.Cg >= 6 * 4096 * kb * cb && w.nstage >= 32 &&
-           kb * cb * g.G * w.nstage >= 6 * num_cus();
+    if (10LL * g.Kg * g.Cg < 6 * 4096 * kb * cb || w.nstage < 32)
+        return false;
+    if (g.R == 5)
+        return g.W % 2 == 0 && 4 * kb * cb * g.G * w.nstage >= 16 * num_cus();
+    return kb * cb * g.G * w.nstage >= 6 * num_cus();
 }
 
 WgradPlan wgrad_direct_rule(const Geom &g)
@@ -1415,16 +1432,17 @@ void wgrad_candidates(const Geom &g, std::vector<WgradPlan> &out)
                     }
         }
     }
+    if (wgrad_wino_applies(g)) {
+        WgradPlan f{};
+        f.tile = -1;
+        f.wino = WINO_PLAN;
+        out.push_back(f);
+    }
     if (out[0].wino == WINO_RULE) {
         WgradPlan d = out[0];
         d.wino = 0;
         d.plain = true;
         out.push_back(d);
-    } else if (wgrad_wino_applies(g)) {
-        WgradPlan f{};
-        f.tile = -1;
-        f.wino = WINO_PLAN;
-        out.push_back(f);
     }
 }
 
@@ -1633,13 +1651,14 @@ int wino_exec(const Geom &g, int M, int cin, const float *src, int src_h, int sr
               void *ws, hipStream_t stream)
 {
     const size_t fb = sizeof(float);
-    const size_t u_bytes = wino_filter_words(M, cin, g.G) * fb;
+    const size_t u_bytes = wino_filter_words(M, cin, g.G, g.R) * fb;
     float *U = (float *)((char *)ws + kAlign);
     WinoArgs a{};
     a.M = M;
     a.cin = cin;
     a.groups = g.G;
     a.nimg = g.N;
+    a.R = g.R;
     a.w = w;
     a.flip = flip;
     a.u_bytes = (uint32_t)u_bytes;
@@ -1662,7 +1681,7 @@ int wino_exec(const Geom &g, int M, int cin, const float *src, int src_h, int sr
     a.before = tl_events.before;
     a.after = tl_events.after;
     return launch_status(
-        launch_wino(a, wino_plan(M, cin, g.G, g.N, Pout, Qout, num_cus()), U, stream));
+        launch_wino(a, wino_plan(M, cin, g.G, g.R, g.N, Pout, Qout, num_cus()), U, stream));
 }
 
 // Forward GEMM launches over n images of geometry g (images from src, outputs
@@ -2104,7 +2123,7 @@ int bwd_exec(const Geom &g, BwdPlan plan, const float *dy, const float *w, float
     if (plan.bt)
         return ip_bwd_data(g, plan, dy, w, dx, ws, stream);
     if (plan.img.wino)
-        return wino_exec(g, g.Cg, g.Kg, dy, g.P, g.Q, H, W, g.pad - 2, true, w, nullptr, dx, ws,
+        return wino_exec(g, g.Cg, g.Kg, dy, g.P, g.Q, H, W, g.pad - (g.R - 1), true, w, nullptr, dx, ws,
                          stream);
 
     const long long xi = (long long)C * H * W, yi = (long long)K * g.P * g.Q;
@@ -2209,6 +2228,7 @@ int wgrad_exec(const Geom &g, WgradPlan p, const float *x, const float *dy, floa
         a.Cg = g.Cg;
         a.groups = g.G;
         a.nimg = N;
+        a.R = R;
         a.x = x;
         a.dy = dy;
         a.x_img_words = (uint32_t)((size_t)C * H * W);
@@ -2236,7 +2256,7 @@ int wgrad_exec(const Geom &g, WgradPlan p, const float *x, const float *dy, floa
         a.before = tl_events.before;
         a.after = tl_events.after;
         int cw;
-        const WinoWork work = wino_wgrad_plan(g.Kg, g.Cg, g.G, N, g.P, g.Q, num_cus(), &cw);
+        const WinoWork work = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, N, g.P, g.Q, num_cus(), &cw);
         return launch_status(launch_wino_wgrad(a, work, cw, stream));
     }
     if (p.img >= 0) {
@@ -2400,36 +2420,33 @@ int candidate_count(int pass, const Geom &g)
     }
 }
 
-// Workspace with which a plan runs as it does with any larger one (the rule's
-// fast filtering: the larger of its own and the direct plan's), and the least
-// with which it runs at all (the smaller).
+// Workspace that candidate `index` asks for.  Of the rule where it uses fast
+// filtering: the direct plan's behind it (the list names fast filtering's own
+// need with the candidate of that name), or, least, the smaller of the two,
+// with which it runs one way or the other.
 size_t fwd_need(const Geom &g, ImgPlan p, bool least = false)
 {
-    size_t n = fwd_ws(g, p);
-    if (p.wino == WINO_RULE) {
-        p.wino = 0;
-        n = least ? std::min(n, fwd_ws(g, p)) : std::max(n, fwd_ws(g, p));
-    }
-    return n;
+    if (p.wino != WINO_RULE)
+        return fwd_ws(g, p);
+    const size_t fast = fwd_ws(g, p);
+    p.wino = 0;
+    return least ? std::min(fast, fwd_ws(g, p)) : fwd_ws(g, p);
 }
 size_t bwd_need(const Geom &g, BwdPlan p, bool least = false)
 {
-    size_t n = bwd_ws(g, p);
-    if (p.img.wino == WINO_RULE) {
-        p.img.wino = 0;
-        n = least ? std::min(n, bwd_ws(g, p)) : std::max(n, bwd_ws(g, p));
-    }
-    return n;
+    if (p.img.wino != WINO_RULE)
+        return bwd_ws(g, p);
+    const size_t fast = bwd_ws(g, p);
+    p.img.wino = 0;
+    return least ? std::min(fast, bwd_ws(g, p)) : bwd_ws(g, p);
 }
-
 size_t wgrad_need(const Geom &g, WgradPlan p, bool least = false)
 {
-    size_t n = wgrad_ws(g, p);
-    if (p.wino == WINO_RULE) {
-        p.wino = 0;
-        n = least ? std::min(n, wgrad_ws(g, p)) : std::max(n, wgrad_ws(g, p));
-    }
-    return n;
+    if (p.wino != WINO_RULE)
+        return wgrad_ws(g, p);
+    const size_t fast = wgrad_ws(g, p);
+    p.wino = 0;
+    return least ? std::min(fast, wgrad_ws(g, p)) : wgrad_ws(g, p);
 }
 
 size_t candidate_ws(int pass, const Geom &g, int index, bool least = false)

@@ -182,8 +182,8 @@ bool wgrad_halo_supported(int TW, int P, int Q, int W);
 hipError_t launch_wgrad_halo(const WgradHaloArgs &a, hipStream_t stream);
 
 // ---------------------------------------------------------------------------
-// Fast filtering F(2x2, 3x3) of a stride-1 3 x 3 problem (forward, or the one
-// phase of backward-data): M rows per group (output channels), cin source
+// Fast filtering F(2x2, 3x3) of a stride-1 R x R problem, R = 3, or 5 in four
+// 3 x 3 parts (forward, or the one phase of backward-data): M rows per group (output channels), cin source
 // channels per group (a multiple of 8), output grid P x Q of 2 x 2 tiles whose
 // 4 x 4 source patch starts at (2 ty + off, 2 tx + off), zero outside the
 // source.  Tiles are numbered over (image, tile row, tile column); an output
@@ -198,7 +198,7 @@ struct WinoWork {
     FastDiv d_nstage;
 };
 struct WinoArgs : WinoWork {
-    int M, cin, groups, nimg;
+    int M, cin, groups, nimg, R;
     const float *w;            // the layer's filters
     int flip;                  // backward-data: rows are input channels, taps mirrored
     uint32_t u_bytes;
@@ -217,11 +217,11 @@ struct WinoArgs : WinoWork {
     hipEvent_t before, after;  // recorded around the GEMM (may be null)
     // Set by launch_wino:
     const float *U;
-    int Pt, Qt, tiles, tblocks, mblocks;
-    FastDiv d_pt, d_qt, d_tblocks, d_mblocks;
+    int Pt, Qt, tiles, tblocks, mblocks, parts, ncb;
+    FastDiv d_pt, d_qt, d_tblocks, d_mblocks, d_ncb;
 };
-size_t wino_filter_words(int M, int cin, int groups);
-WinoWork wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus);
+size_t wino_filter_words(int M, int cin, int groups, int R);
+WinoWork wino_plan(int M, int cin, int groups, int R, int nimg, int P, int Q, int cus);
 size_t wino_slab_bytes(const WinoWork &w);
 // Filter transform (into U), GEMM and finish.
 hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stream);
@@ -229,12 +229,13 @@ hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stre
 // ---------------------------------------------------------------------------
 // Backward-weight of the same layers by F(3x3, 2x2): 2 x 2 tiles of dy, 4 x 4
 // patches of x at (2 ty + off, 2 tx + off) with off = -pad; an output tile is
-// 64 filters x 64 channels of a group (channels fastest), its reduction the
+// 64 filters x 64 channels of a group and one part of the filter (parts, then
+// channels fastest), its reduction the
 // tiles in stages of eight: cw columns of 8 / cw images, in strips that run
 // down the tile rows.
 // ---------------------------------------------------------------------------
 struct WinoWgArgs : WinoWork {
-    int Kg, Cg, groups, nimg;
+    int Kg, Cg, groups, nimg, R;
     const float *x, *dy;
     uint32_t x_bytes, dy_bytes, x_img_words, dy_img_words;
     int H, W, HW, P, Q, PQ, off;
@@ -243,10 +244,10 @@ struct WinoWgArgs : WinoWork {
     float *slabs;
     hipEvent_t before, after;
     // Set by launch_wino_wgrad:
-    int cw, cw_log, Pt, Qt, nstrip, kblocks, cblocks;
-    FastDiv d_pt, d_strips, d_cblocks, d_kblocks;
+    int cw, cw_log, Pt, Qt, nstrip, kblocks, cblocks, parts;
+    FastDiv d_pt, d_strips, d_cblocks, d_kblocks, d_parts;
 };
-WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int nimg, int P, int Q, int cus, int *cw);
+WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int R, int nimg, int P, int Q, int cus, int *cw);
 size_t wino_wgrad_slab_bytes(const WinoWork &w);
 hipError_t launch_wino_wgrad(WinoWgArgs a, const WinoWork &p, int cw, hipStream_t stream);
 

@@ -11,6 +11,13 @@
 //
 // The sum over channels is 16 matrix products (one per point of the
 // transformed tile), run on v_mfma_f32_16x16x4f32 in fp32 throughout.
+//
+// A 5 x 5 filter is the sum of four 3 x 3 ones (parts (a, b), a, b < 2) at
+// offsets (2 a, 2 b): part (a, b) holds the taps (2 a + i, 2 b + j), i, j < 3,
+// without those that an earlier part holds (i = 0 where a > 0, j = 0 where
+// b > 0).  All four add up in the transformed domain, 64 multiplications
+// instead of 100 for 2 x 2 outputs; to the products they are further channels.
+// The offsets are even so that the patches keep their alignment.
 #include "internal.h"
 
 namespace miconv {
@@ -72,34 +79,48 @@ __device__ __forceinline__ f32x4 lds_b128(const float *base, int word)
     return *(LDS_AS const f32x4 *)(base + word);
 }
 
-// The 4 x 4 patch of a tile and channel, by buffer loads: off holds one offset
-// per load (out of range: zero), soff the stage's.  MODE 0: one word each;
-// 1: columns 0, (1, 2), 3; 2: columns (0, 1), (2, 3).
+// A patch row of a tile and channel, by buffer loads: off holds one offset per
+// load (out of range: zero), soff the row's and stage's.  MODE 1 (first column
+// odd): columns 0, (1, 2), 3; MODE 2 (even): columns (0, 1), (2, 3).  The pairs
+// start at even columns, so on even widths a pair lies inside a row or outside;
+// on odd ones (ODD) the pair at the last column takes its second word from
+// past the row, which `keep` (0 for that lane, else all ones) clears.  MODE 0:
+// one word each.
 template <int MODE>
 struct Patch {
     static constexpr int LOADS = MODE == 0 ? 4 : MODE == 1 ? 3 : 2;  // a row
+    // First column of load l, and whether it is a pair.
+    static constexpr int col(int l) { return MODE == 0 ? l : MODE == 1 ? l + l / 2 : 2 * l; }
+    static constexpr bool pair(int l) { return MODE == 2 || (MODE == 1 && l == 1); }
 };
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <int MODE>
-__device__ __forceinline__ void load_patch(__amdgpu_buffer_rsrc_t r,
-                                           const uint32_t (&off)[4 * Patch<MODE>::LOADS],
-                                           uint32_t soff, float (&d)[16])
+__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r, const uint32_t *off,
+                                         uint32_t soff, float *d)
 {
-    constexpr int L = Patch<MODE>::LOADS;
 #pragma unroll
-    for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int l = 0; l < L; l++) {
-            const int c = MODE == 0 ? l : MODE == 1 ? (l ? l + l / 2 : 0) : 2 * l;  // first column
-            if (MODE == 2 || (MODE == 1 && l == 1)) {
-                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off[i * L + l], soff, 0);
-                d[4 * i + c] = __uint_as_float(v[0]);
-                d[4 * i + c + 1] = __uint_as_float(v[1]);
-            } else {
-                d[4 * i + c] =
-                    __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off[i * L + l], soff, 0));
-            }
+    for (int l = 0; l < Patch<MODE>::LOADS; l++) {
+        const int c = Patch<MODE>::col(l);
+        if (Patch<MODE>::pair(l)) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off[l], soff, 0);
+            const uint32_t hi = v[1];
+            d[c] = __uint_as_float(v[0]);
+            d[c + 1] = __uint_as_float(hi);
+        } else {
+            d[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off[l], soff, 0));
         }
+    }
+}
+// Clears the words past the row (once the loads are due).
+template <int MODE>
+__device__ __forceinline__ void clear_past(const uint32_t (&keep)[2], float *d)
+{
+    if (MODE == 1) {
+        d[2] = __uint_as_float(__float_as_uint(d[2]) & keep[0]);
+    } else {
+        d[1] = __uint_as_float(__float_as_uint(d[1]) & keep[0]);
+        d[3] = __uint_as_float(__float_as_uint(d[3]) & keep[1]);
+    }
 }
 
 // Whether a sum is neither an infinity nor a NaN.
@@ -245,7 +266,7 @@ __device__ __forceinline__ void store_tile(const WinoArgs &a, const TileAt &at, 
 // (2 %), a raised wave priority around the MFMAs (4 %), one wave a SIMD with 64
 // channels by 16 tiles and the transform in every wave (25 %).
 // ---------------------------------------------------------------------------
-template <int MODE>
+template <int MODE, bool ODD>
 __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
 {
     constexpr int STG = 2 * 4 * 4 * 256;  // words of U, and of V, per stage
@@ -264,44 +285,65 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.src, a.src_bytes);
     const __amdgpu_buffer_rsrc_t rU = make_rsrc(a.U, a.u_bytes);
     const uint32_t stage_bytes = 32u * (uint32_t)a.src_hw;
+    const int ncb = a.ncb;
 
     // Cursor of the loads, two stages ahead of the MFMAs.
     Unit pu{};
     int pk = -1, ps = 0;     // unit, stage
+    int pc = 0;              // its channel block (of the part)
     uint32_t pu_base = 0;    // its filters
     uint32_t off[NOFF];      // its patches
+    uint32_t keep[2] = {~0u, ~0u};
     bool more = true;
     auto advance = [&]() __attribute__((always_inline)) {
-        if (pk >= 0 && ++ps < pu.s1)
-            return;
-        const WinoArgs &a = cold_args<WinoArgs>();
-        const int nunits = a.rounds + (a.rest ? 2 : 0);
-        do {
-            if (++pk >= nunits) {
-                more = false;
+        if (pk >= 0) {
+            ps++;
+            pc++;
+            if (ps < pu.s1 && pc < ncb)
                 return;
-            }
-            pu = wino_unit(a, w, pk);
-        } while (pu.s0 >= pu.s1);
-        ps = pu.s0;
+        }
+        const WinoArgs &a = cold_args<WinoArgs>();
+        if (pk < 0 || ps >= pu.s1) {
+            const int nunits = a.rounds + (a.rest ? 2 : 0);
+            do {
+                if (++pk >= nunits) {
+                    more = false;
+                    return;
+                }
+                pu = wino_unit(a, w, pk);
+            } while (pu.s0 >= pu.s1);
+            ps = pu.s0;
+        }
+        const int part = (int)fast_div((uint32_t)ps, a.d_ncb);
+        pc = ps - part * ncb;
+        const int ph = part / a.parts, pw = part - ph * a.parts;
         const int gm = (int)fast_div((uint32_t)pu.tile, a.d_tblocks);  // (group, channel block)
         const int tb = pu.tile - gm * a.tblocks, g = (int)fast_div((uint32_t)gm, a.d_mblocks);
         pu_base = (uint32_t)gm * (uint32_t)a.nstage * (STG * 4u);
         const int t = tb * 64 + tg * 16 + lc;
         const TileAt at = tile_at(a, min(t, a.tiles - 1));
-        const int h0 = 2 * at.ty + a.off, w0 = 2 * at.tx + a.off;
+        const int h0 = 2 * (at.ty + ph) + a.off, w0 = 2 * (at.tx + pw) + a.off;
         const uint32_t base = ((uint32_t)at.img * a.src_img_words +
                                (uint32_t)(g * a.cin + 4 * half + kr) * (uint32_t)a.src_hw) * 4u;
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
             for (int l = 0; l < Patch<MODE>::LOADS; l++) {
-                const int c = MODE == 0 ? l : MODE == 1 ? (l ? l + l / 2 : 0) : 2 * l;
+                const int c = Patch<MODE>::col(l);
                 const bool ok = (unsigned)(h0 + i) < (unsigned)a.src_h &&
                                 (unsigned)(w0 + c) < (unsigned)a.src_w;
                 off[i * Patch<MODE>::LOADS + l] =
                     ok ? base + (uint32_t)((h0 + i) * a.src_w + w0 + c) * 4u : kOob;
             }
+        if constexpr (ODD) {
+            keep[0] = w0 + (MODE == 1 ? 2 : 1) == a.src_w ? 0u : ~0u;
+            keep[1] = w0 + 3 == a.src_w ? 0u : ~0u;
+        }
+    };
+    auto load_patch = [&](float (&d)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            load_row<MODE>(rX, off + i * Patch<MODE>::LOADS, (uint32_t)pc * stage_bytes, d + 4 * i);
     };
     auto load_u = [&](float *Ud, uint32_t base, int s) __attribute__((always_inline)) {
 #pragma unroll
@@ -311,8 +353,14 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
                   base + (uint32_t)s * (STG * 4u));
         }
     };
-    auto write_v = [&](float *Vd, const float (&d)[16]) __attribute__((always_inline)) {
+    // (Before the cursor moves on: keep is that of the patches in d.)
+    auto write_v = [&](float *Vd, float (&d)[16]) __attribute__((always_inline)) {
         float v[16];
+        if constexpr (ODD) {
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                clear_past<MODE>(keep, d + 4 * i);
+        }
         input_transform(d, v);
 #pragma unroll
         for (int q = 0; q < 4; q++)
@@ -451,7 +499,7 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
                 advance();
                 have2 = more;
                 if (have2)
-                    load_patch<MODE>(rX, off, (uint32_t)ps * stage_bytes, d);
+                    load_patch(d);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -469,14 +517,14 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     if (!more)
         return;
     load_u(U0, pu_base, ps);
-    load_patch<MODE>(rX, off, (uint32_t)ps * stage_bytes, d);
+    load_patch(d);
     write_v(V0, d);
     step_cursor();
     advance();
     have1 = more;
     if (have1) {
         load_u(U1, pu_base, ps);
-        load_patch<MODE>(rX, off, (uint32_t)ps * stage_bytes, d);
+        load_patch(d);
     }
     clear();
     __builtin_amdgcn_s_waitcnt(0);
@@ -497,13 +545,14 @@ __device__ float wino_direct(const WinoArgs &a, int img, int oc, int p, int q)
     float s = 0.f;
     for (int c = 0; c < a.cin && s == s; c++) {  // (a NaN stays one)
         const float *x = a.src + (size_t)img * a.src_img_words + (size_t)(g * a.cin + c) * a.src_hw;
-        const float *wt = a.flip ? a.w + ((size_t)(g * a.cin + c) * a.M + m) * 9
-                                 : a.w + ((size_t)(g * a.M + m) * a.cin + c) * 9;
-        for (int r = 0; r < 3; r++)
-            for (int z = 0; z < 3; z++) {
-                const int h = p + a.off + r, w = q + a.off + z, k = r * 3 + z;
+        const int taps = a.R * a.R;
+        const float *wt = a.flip ? a.w + ((size_t)(g * a.cin + c) * a.M + m) * taps
+                                 : a.w + ((size_t)(g * a.M + m) * a.cin + c) * taps;
+        for (int r = 0; r < a.R; r++)
+            for (int z = 0; z < a.R; z++) {
+                const int h = p + a.off + r, w = q + a.off + z, k = r * a.R + z;
                 if ((unsigned)h < (unsigned)a.src_h && (unsigned)w < (unsigned)a.src_w)
-                    s = fmaf(x[h * a.src_w + w], wt[a.flip ? 8 - k : k], s);
+                    s = fmaf(x[h * a.src_w + w], wt[a.flip ? taps - 1 - k : k], s);
             }
     }
     return s + (a.bias ? a.bias[oc] : 0.f);
@@ -582,8 +631,8 @@ __global__ __launch_bounds__(256) void wino_finish_kernel(const WinoArgs a)
 
 // Filter transform U = G g Gt into the order the GEMM reads: word
 // ((((gm nstage + s) 2 + step) 4 + b) 4 + q) 256 + lane 4 + j is point 4 q + j
-// of row m = 64 mb + 16 b + lane % 16, channel c = 8 s + 4 step + lane / 16 of
-// group g, gm = g mblocks + mb (zero past M).  flip (backward-data): row m is
+// of row m = 64 mb + 16 b + lane % 16, channel c = 8 (s % ncb) + 4 step + lane / 16
+// of group g, gm = g mblocks + mb (zero past M), part s / ncb of the filter.  flip (backward-data): row m is
 // input channel m, channel c filter c, the taps mirrored.  Also lowers the flag.
 __global__ __launch_bounds__(256) void wino_filter_kernel(const WinoArgs a, float *__restrict__ U)
 {
@@ -593,14 +642,20 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(const WinoArgs a, floa
     const int lane = i & 63, b = (i >> 6) & 3, step = (i >> 8) & 1;
     const int r = i >> 9, gm = r / a.nstage, s = r - gm * a.nstage;
     const int g = gm / a.mblocks, mb = gm - g * a.mblocks;
-    const int m = mb * 64 + b * 16 + (lane & 15), c = s * 8 + step * 4 + (lane >> 4);
+    const int part = s / a.ncb, ph = part / a.parts, pw = part - ph * a.parts;
+    const int m = mb * 64 + b * 16 + (lane & 15);
+    const int c = (s - part * a.ncb) * 8 + step * 4 + (lane >> 4);
     float k[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (m < a.M) {
-        const float *src = a.flip ? a.w + ((size_t)(g * a.cin + c) * a.M + m) * 9
-                                  : a.w + ((size_t)(g * a.M + m) * a.cin + c) * 9;
+        const int taps = a.R * a.R;
+        const float *src = a.flip ? a.w + ((size_t)(g * a.cin + c) * a.M + m) * taps
+                                  : a.w + ((size_t)(g * a.M + m) * a.cin + c) * taps;
 #pragma unroll
-        for (int j = 0; j < 9; j++)
-            k[j] = src[a.flip ? 8 - j : j];
+        for (int j = 0; j < 9; j++) {
+            const int i = j / 3, z = j - 3 * i, t = (2 * ph + i) * a.R + 2 * pw + z;
+            if ((ph == 0 || i > 0) && (pw == 0 || z > 0))
+                k[j] = src[a.flip ? taps - 1 - t : t];
+        }
     }
     float t[12];
 #pragma unroll
@@ -689,23 +744,20 @@ __device__ __forceinline__ void tap_transform(const float (&m)[16], float (&w)[9
     }
 }
 
-// One row of a patch (MODE as in load_patch), at the row's scalar offset.
-template <int MODE>
-__device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r,
-                                         const uint32_t (&off)[Patch<MODE>::LOADS], uint32_t soff,
-                                         float *d)
+// Output tile: part of the filter, channel block and (group, filter block).
+struct WgTile {
+    int gm, cb, part, ph, pw;
+};
+__device__ __forceinline__ WgTile wg_tile(const WinoWgArgs &a, int tile)
 {
-#pragma unroll
-    for (int l = 0; l < Patch<MODE>::LOADS; l++) {
-        const int c = MODE == 0 ? l : MODE == 1 ? (l ? l + l / 2 : 0) : 2 * l;
-        if (MODE == 2 || (MODE == 1 && l == 1)) {
-            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off[l], soff, 0);
-            d[c] = __uint_as_float(v[0]);
-            d[c + 1] = __uint_as_float(v[1]);
-        } else {
-            d[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off[l], soff, 0));
-        }
-    }
+    WgTile t;
+    const int n = (int)fast_div((uint32_t)tile, a.d_parts);
+    t.part = tile - n * a.parts * a.parts;
+    t.ph = t.part / a.parts;
+    t.pw = t.part - t.ph * a.parts;
+    t.gm = (int)fast_div((uint32_t)n, a.d_cblocks);
+    t.cb = n - t.gm * a.cblocks;
+    return t;
 }
 
 }  // namespace
@@ -713,7 +765,10 @@ __device__ __forceinline__ void load_row(__amdgpu_buffer_rsrc_t r,
 template <int MODE>
 __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
 {
-    constexpr int XL = Patch<MODE>::LOADS, YL = MODE == 0 ? 2 : 1;  // loads a row
+    // Loads a row of a patch and of dy.  (Odd widths load single words: pairs
+    // cleared as in wino_gemm_kernel take registers that this kernel lacks, 0.274
+    // instead of 0.196 ms on 13 x 13 maps.)
+    constexpr int XL = Patch<MODE>::LOADS, YL = MODE == 0 ? 2 : 1;
     __shared__ __attribute__((aligned(16))) float Y0[WG_STG], Y1[WG_STG], X0[WG_STG], X1[WG_STG];
 
     const int lane = threadIdx.x & 63;
@@ -737,7 +792,7 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
 
     // Cursor of the loads, two stages ahead of the MFMAs.
     Unit pu{};
-    int pk = -1, ps = 0, pty = 0;
+    int pk = -1, ps = 0, pty = 0, ph0 = 0;  // unit, stage, tile row, first patch row of row 0
     bool more = true, fresh = true;      // fresh: the strip's first stage here
     uint32_t xo[XL], yo[YL];
     auto advance = [&]() __attribute__((always_inline)) {
@@ -764,17 +819,19 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
         const int st = (int)fast_div((uint32_t)ps, c.d_pt);  // (image group, strip)
         pty = ps - st * c.Pt;
         const int ig = (int)fast_div((uint32_t)st, c.d_strips), strip = st - ig * c.nstrip;
-        const int gm = (int)fast_div((uint32_t)pu.tile, c.d_cblocks), cb = pu.tile - gm * c.cblocks;
+        const WgTile tile = wg_tile(c, pu.tile);
+        const int cb = tile.cb, gm = tile.gm;
         const int g = (int)fast_div((uint32_t)gm, c.d_kblocks), kb = gm - g * c.kblocks;
         const int tx = strip * c.cw + (tl & (c.cw - 1));
         const int img = ig * (8 >> c.cw_log) + (tl >> c.cw_log);
         const int k = kb * 64 + wave * 8 + c8, ch = cb * 64 + wave * 8 + c8;
         const bool in = tx < c.Qt && img < c.nimg;
-        const int w0 = 2 * tx + c.off;
+        const int w0 = 2 * (tx + tile.pw) + c.off;
+        ph0 = 2 * tile.ph + c.off;
         const uint32_t xb = ((uint32_t)img * c.x_img_words + (uint32_t)((g * c.Cg + ch) * c.HW)) * 4u;
 #pragma unroll
         for (int l = 0; l < XL; l++) {
-            const int col = w0 + (MODE == 0 ? l : MODE == 1 ? (l ? l + l / 2 : 0) : 2 * l);
+            const int col = w0 + Patch<MODE>::col(l);
             xo[l] = in && ch < c.Cg && (unsigned)col < (unsigned)c.W ? xb + (uint32_t)col * 4u : kOob;
         }
         const uint32_t yb = ((uint32_t)img * c.dy_img_words + (uint32_t)((g * c.Kg + k) * c.PQ)) * 4u;
@@ -788,7 +845,7 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
     auto load_x = [&](int i, float (&d)[8]) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < 2; r++) {
-            const int h = 2 * pty + a.off + i + r;
+            const int h = 2 * pty + ph0 + i + r;
             const bool ok = more && (unsigned)h < (unsigned)a.H;
             load_row<MODE>(make_rsrc(a.x, ok ? a.x_bytes : 0u), xo,
                            ok ? (uint32_t)(h * a.W) * 4u : 0u, d + 4 * r);
@@ -802,12 +859,14 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
             const uint32_t soff = ok ? (uint32_t)((2 * pty + r) * a.Q) * 4u : 0u;
             if constexpr (YL == 1) {
                 const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rY, (int)yo[0], soff, 0);
+                const uint32_t hi = v[1];
                 g[2 * r] = __uint_as_float(v[0]);
-                g[2 * r + 1] = __uint_as_float(v[1]);
+                g[2 * r + 1] = __uint_as_float(hi);
             } else {
-                g[2 * r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rY, (int)yo[0], soff, 0));
-                g[2 * r + 1] =
-                    __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rY, (int)yo[YL - 1], soff, 0));
+#pragma unroll
+                for (int l = 0; l < YL; l++)
+                    g[2 * r + l] =
+                        __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rY, (int)yo[l], soff, 0));
             }
         }
     };
@@ -851,11 +910,13 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
     // add: onto what an earlier part of the unit has stored there.
     auto finish = [&](const Unit &un, bool add, bool end, float bias) __attribute__((always_inline)) {
         const WinoWgArgs &c = cold_args<WinoWgArgs>();
-        const int gm = (int)fast_div((uint32_t)un.tile, c.d_cblocks), cb = un.tile - gm * c.cblocks;
+        const WgTile tile = wg_tile(c, un.tile);
+        const int cb = tile.cb, gm = tile.gm, part = tile.part;
         const int g = (int)fast_div((uint32_t)gm, c.d_kblocks), kb = gm - g * c.kblocks;
         float *const slab = un.slab >= 0 ? c.slabs + (size_t)un.slab * WG_SLAB : nullptr;
         const int Kg = c.Kg, Cg = c.Cg, ch = cb * 64 + cg * 16 + lc;
-        float *const dw = c.dw + (size_t)g * Kg * Cg * 9;
+        const int R = c.R, i0 = tile.ph > 0, j0 = tile.pw > 0;  // taps that an earlier part holds
+        float *const dw = c.dw + (size_t)g * Kg * Cg * R * R + 2 * tile.ph * R + 2 * tile.pw;
 #pragma unroll
         for (int b = 0; b < 2; b++)
 #pragma unroll
@@ -866,16 +927,29 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
                 for (int p = 0; p < 16; p++)
                     x[p] = acc[b][p][r];
                 tap_transform(x, t);
-                float *const o = slab ? slab + (row * 64 + cg * 16 + lc) * 9
-                                      : dw + ((size_t)k * Cg + ch) * 9;
-                if (slab || (k < Kg && ch < Cg)) {
-                    if (add)
+                // (Loads together, then stores: not each store behind its load.)
+                if (slab) {
+                    float *const o = slab + (row * 64 + cg * 16 + lc) * 9;
+                    if (add) {
 #pragma unroll
                         for (int j = 0; j < 9; j++)
                             t[j] += o[j];
+                    }
 #pragma unroll
                     for (int j = 0; j < 9; j++)
                         o[j] = t[j];
+                } else if (k < Kg && ch < Cg) {
+                    float *const o = dw + ((size_t)k * Cg + ch) * R * R;
+                    if (add) {
+#pragma unroll
+                        for (int j = 0; j < 9; j++)
+                            if (j / 3 >= i0 && j % 3 >= j0)
+                                t[j] += o[j / 3 * R + j % 3];
+                    }
+#pragma unroll
+                    for (int j = 0; j < 9; j++)
+                        if (j / 3 >= i0 && j % 3 >= j0)
+                            o[j / 3 * R + j % 3] = t[j];
                 }
             }
         if (!end)
@@ -887,7 +961,7 @@ __global__ __launch_bounds__(512, 2) void wino_wgrad_kernel(const WinoWgArgs a)
         if (tl == 0) {
             if (slab)
                 slab[64 * 64 * 9 + wave * 8 + c8] = bias;
-            else if (c.db && cb == 0 && kb * 64 + wave * 8 + c8 < Kg)
+            else if (c.db && cb == 0 && part == 0 && kb * 64 + wave * 8 + c8 < Kg)
                 c.db[g * Kg + kb * 64 + wave * 8 + c8] = bias;
         }
     };
@@ -1009,9 +1083,19 @@ __global__ __launch_bounds__(256) void wino_wgrad_finish_kernel(const WinoWgArgs
     const int tile = blockIdx.x / WG_BLOCKS, r = tile - a.rounds * a.nwg;
     const int lane = threadIdx.x & 31, j = threadIdx.x >> 5;
     const int e = ((blockIdx.x - tile * WG_BLOCKS) * 32 + lane) * 4;
-    const int gm = tile / a.cblocks, cb = tile - gm * a.cblocks;
-    const int g = gm / a.kblocks, kb = gm - g * a.kblocks;
-    float *const dw = a.dw + ((size_t)(g * a.Kg + kb * 64) * a.Cg + cb * 64) * 9;
+    const WgTile wt = wg_tile(a, tile);
+    const int gm = wt.gm, cb = wt.cb, g = gm / a.kblocks, kb = gm - g * a.kblocks, taps = a.R * a.R;
+    // Word m of filter row `row` of the tile: channel m / 9, tap (m % 9 / 3, m % 3)
+    // of the part; -1 for a tap that an earlier part holds.
+    float *const dw = a.dw + ((size_t)(g * a.Kg + kb * 64) * a.Cg + cb * 64) * taps;
+    auto place = [&](int row, int m) {
+        if (a.parts == 1)
+            return (long long)row * a.Cg * 9 + m;
+        const int c = m / 9, i = (m - c * 9) / 3, z = m - c * 9 - i * 3;
+        return (i == 0 && wt.ph > 0) || (z == 0 && wt.pw > 0)
+                   ? -1LL
+                   : ((long long)row * a.Cg + c) * taps + (2 * wt.ph + i) * a.R + 2 * wt.pw + z;
+    };
     const int hi = (r + 1) * a.nstage, w0 = r >= 0 ? wino_first_share(a, r) : 0;
     const bool cut = r >= 0 && share(a, w0 + 1) < hi;  // else its workgroup has written dw
     f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1038,13 +1122,15 @@ __global__ __launch_bounds__(256) void wino_wgrad_finish_kernel(const WinoWgArgs
             const int n = e + i, row = n / 576, m = n - row * 576;
             if (n >= 64 * 64 * 9) {
                 const int k = kb * 64 + n - 64 * 64 * 9;
-                if (cut && a.db && cb == 0 && k < a.Kg)
+                if (cut && a.db && cb == 0 && wt.part == 0 && k < a.Kg)
                     a.db[g * a.Kg + k] = s[i];
             } else if (kb * 64 + row < a.Kg && cb * 64 + m / 9 < a.Cg) {
-                float *const o = dw + (size_t)row * a.Cg * 9 + m;
+                const long long at = place(row, m);
+                if (at < 0)
+                    continue;
                 if (cut)
-                    *o = s[i];
-                mask |= is_finite(cut ? s[i] : *o) ? 0 : 1 << i;
+                    dw[at] = s[i];
+                mask |= is_finite(cut ? s[i] : dw[at]) ? 0 : 1 << i;
             }
         }
     }
@@ -1057,13 +1143,14 @@ __global__ __launch_bounds__(256) void wino_wgrad_finish_kernel(const WinoWgArgs
         if (!(bad[i >> 2] >> (i & 3) & 1))
             continue;
         const int n = (blockIdx.x - tile * WG_BLOCKS) * 128 + i, row = n / 576, m = n - row * 576;
-        const int c = cb * 64 + m / 9, tap = m % 9;
+        const int c = cb * 64 + m / 9;
+        const int r0 = 2 * wt.ph + m % 9 / 3 + a.off, z0 = 2 * wt.pw + m % 3 + a.off;
         const float *x = a.x + (size_t)(g * a.Cg + c) * a.HW;
         const float *dy = a.dy + (size_t)(g * a.Kg + kb * 64 + row) * a.PQ;
         float v = 0.f;
         for (int img = 0; img < a.nimg; img++, x += a.x_img_words, dy += a.dy_img_words) {
             for (int pq = threadIdx.x; pq < a.PQ; pq += 256) {
-                const int p = pq / a.Q, h = p + a.off + tap / 3, w = pq - p * a.Q + a.off + tap % 3;
+                const int p = pq / a.Q, h = p + r0, w = pq - p * a.Q + z0;
                 if ((unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
                     v = fmaf(dy[pq], x[h * a.W + w], v);
             }
@@ -1077,15 +1164,21 @@ __global__ __launch_bounds__(256) void wino_wgrad_finish_kernel(const WinoWgArgs
                 sum[threadIdx.x] += sum[threadIdx.x + k];
         }
         if (threadIdx.x == 0)
-            dw[(size_t)row * a.Cg * 9 + m] = sum[0];
+            dw[place(row, m)] = sum[0];
     }
 }
 
 // ---------------------------------------------------------------- launches
-// Channel blocks of 64, stages of 8 channels (cin is a multiple of 8).
-size_t wino_filter_words(int M, int cin, int groups)
+// Parts of an R x R filter along an axis (R = 3 or 5).
+static int wino_parts(int R)
 {
-    return (size_t)groups * ((M + 63) / 64) * (cin / 8) * 8192;
+    return (R - 1) / 2;
+}
+
+// Channel blocks of 64, stages of 8 channels (cin is a multiple of 8) of a part.
+size_t wino_filter_words(int M, int cin, int groups, int R)
+{
+    return (size_t)groups * ((M + 63) / 64) * (cin / 8) * wino_parts(R) * wino_parts(R) * 8192;
 }
 
 // Work of n output tiles of nstage stages on cus workgroups, each at least
@@ -1104,10 +1197,11 @@ static WinoWork wino_work(long long n, int nstage, int cus, int least)
     return w;
 }
 
-WinoWork wino_plan(int M, int cin, int groups, int nimg, int P, int Q, int cus)
+WinoWork wino_plan(int M, int cin, int groups, int R, int nimg, int P, int Q, int cus)
 {
     const long long tiles = (long long)nimg * ((P + 1) / 2) * ((Q + 1) / 2);
-    return wino_work((long long)groups * ((M + 63) / 64) * ((tiles + 63) / 64), cin / 8, cus, 4);
+    return wino_work((long long)groups * ((M + 63) / 64) * ((tiles + 63) / 64),
+                     cin / 8 * wino_parts(R) * wino_parts(R), cus, 4);
 }
 
 size_t wino_slab_bytes(const WinoWork &w)
@@ -1124,6 +1218,9 @@ hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stre
     a.tiles = a.nimg * a.Pt * a.Qt;
     a.tblocks = (a.tiles + 63) / 64;
     a.mblocks = (a.M + 63) / 64;
+    a.parts = wino_parts(a.R);
+    a.ncb = a.cin / 8;
+    a.d_ncb = make_fastdiv(a.ncb);
     a.d_tblocks = make_fastdiv(a.tblocks);
     a.d_mblocks = make_fastdiv(a.mblocks);
     a.d_qt = make_fastdiv(a.Qt);
@@ -1135,15 +1232,16 @@ hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stre
         return e;
     if (a.before && (e = hipEventRecord(a.before, stream)) != hipSuccess)
         return e;
-    // Pairs of columns load together where no pair straddles the map's edge:
-    // even widths, from the column whose number is even.
     const dim3 grid((unsigned)p.nwg);
-    if (a.src_w & 1)
-        wino_gemm_kernel<0><<<grid, 512, 0, stream>>>(a);
-    else if (a.off & 1)
-        wino_gemm_kernel<1><<<grid, 512, 0, stream>>>(a);
+    const int mode = (a.off & 1 ? 0 : 2) + (a.src_w & 1);
+    if (mode == 0)
+        wino_gemm_kernel<1, false><<<grid, 512, 0, stream>>>(a);
+    else if (mode == 1)
+        wino_gemm_kernel<1, true><<<grid, 512, 0, stream>>>(a);
+    else if (mode == 2)
+        wino_gemm_kernel<2, false><<<grid, 512, 0, stream>>>(a);
     else
-        wino_gemm_kernel<2><<<grid, 512, 0, stream>>>(a);
+        wino_gemm_kernel<2, true><<<grid, 512, 0, stream>>>(a);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     if (a.after && (e = hipEventRecord(a.after, stream)) != hipSuccess)
@@ -1157,7 +1255,7 @@ hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stre
 // 0.521 ms with 2 columns, 0.560 with 8; one column of eight images was 17-28 %
 // slower than 8 columns with one idle on 14 x 14 maps: its loads touch eight
 // times the cache lines).
-WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int nimg, int P, int Q, int cus, int *cw)
+WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int R, int nimg, int P, int Q, int cus, int *cw)
 {
     const int Pt = (P + 1) / 2, Qt = (Q + 1) / 2;
     auto strips = [&](int c) { return (long long)((Qt + c - 1) / c) * ((nimg + 8 / c - 1) / (8 / c)); };
@@ -1165,7 +1263,7 @@ WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int nimg, int P, int Q, int
     for (int c : {4, 2})
         if (strips(c) < strips(*cw))
             *cw = c;
-    return wino_work((long long)groups * ((Kg + 63) / 64) * ((Cg + 63) / 64),
+    return wino_work((long long)groups * ((Kg + 63) / 64) * ((Cg + 63) / 64) * wino_parts(R) * wino_parts(R),
                      (int)(strips(*cw) * Pt), cus, 8);
 }
 
@@ -1186,6 +1284,8 @@ hipError_t launch_wino_wgrad(WinoWgArgs a, const WinoWork &p, int cw, hipStream_
     a.cblocks = (a.Cg + 63) / 64;
     a.d_pt = make_fastdiv(a.Pt);
     a.d_strips = make_fastdiv(a.nstrip);
+    a.parts = wino_parts(a.R);
+    a.d_parts = make_fastdiv(a.parts * a.parts);
     a.d_cblocks = make_fastdiv(a.cblocks);
     a.d_kblocks = make_fastdiv(a.kblocks);
     hipError_t e;
