@@ -556,10 +556,11 @@ def _bench_config(cfg, args, with_cpu):
     F = flops_of(drun.L)
     ai = F / bytes_of(drun.L, dom["pass"])
     if ai >= ridge:
-        # Fast filtering executes 16 of a direct sum's 36 multiplications (on
-        # whole 2x2 tiles): the roofline counts what is executed.
+        # Fast filtering executes 16 of a direct sum's 36 multiplications, 64
+        # of 100 with 5x5 filters (on whole 2x2 tiles): the roofline counts
+        # what is executed.
         fast = getattr(drun, "fast", lambda p: False)(dom["pass"])
-        ach = F * (16 / 36 if fast else 1) / k_ms / 1e9
+        ach = F * ((16 / 36 if drun.L.shape[5] == 3 else 64 / 100) if fast else 1) / k_ms / 1e9
         roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(ach / PEAK_TFLOPS, 4), "traffic": None}
     else:
