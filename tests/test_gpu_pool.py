@@ -100,6 +100,58 @@ def test_pool_random_shapes(mode, pshape):
     assert_within(dx, dx_ref, adx, f"{mode} pool bwd {pshape}")
 
 
+# 2 x 2 and 3 x 3 windows at stride 2 have kernels of their own: several small
+# planes a workgroup (about 1024 elements), planes up to 48 KiB, windows all
+# inside the image or not, words past a multiple of four.
+@pytest.mark.parametrize("mode", ["max", "avg"])
+@pytest.mark.parametrize("pshape", [
+    (3, 7, 13, 13, 3, 3, 2, 0),     # six planes a workgroup, a ragged last one
+    (1, 5, 3, 2, 2, 2, 2, 0),       # all planes in one workgroup
+    (2, 600, 1, 1, 2, 2, 2, 1),     # one element a plane
+    (1, 3, 3, 1, 3, 3, 2, 2),       # windows wider than the padded rows allow
+    (2, 3, 55, 55, 3, 3, 2, 0),     # odd planes, windows inside
+    (1, 3, 56, 57, 3, 3, 2, 0),     # overhang on one axis
+    (1, 3, 57, 56, 3, 3, 2, 1),
+    (1, 2, 33, 34, 3, 3, 2, 2),
+    (1, 2, 110, 111, 3, 3, 2, 0),   # the largest planes of the forward kernel
+    (1, 2, 110, 111, 2, 2, 2, 1),
+    (1, 2, 112, 112, 2, 2, 2, 0),   # larger: forward per element, backward here
+], ids=str)
+def test_stride_2_windows(mode, pshape):
+    N, C, H, W, R, S, st, pad = pshape
+    rng = np.random.default_rng(list(pshape) + [11])
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    x[rng.random(x.shape) < 0.3] = 0  # ties
+    y_ref, ay, mask_ref = oracle.pool_fwd(mode, pshape, x)
+    dy = rng.standard_normal(y_ref.shape).astype(np.float32)
+    y, mask, dx = _pool_gpu(mode, pshape, x, dy)
+    if mode == "max":
+        assert np.array_equal(y.astype(np.float64), y_ref)
+        assert np.array_equal(mask.astype(np.int64), mask_ref)
+    else:
+        assert_within(y, y_ref, ay, f"avg pool fwd {pshape}")
+    dx_ref, adx = oracle.pool_bwd(mode, pshape, dy, mask_ref)
+    assert_within(dx, dx_ref, adx, f"{mode} pool bwd {pshape}")
+
+
+@pytest.mark.parametrize("F", [2, 3])
+def test_stride_2_windows_of_infinities_and_nans(F):
+    """As the general kernels (a window of the same size whose stride differs
+    only where there is a single window along the axis): a NaN never wins, a
+    window without a larger value keeps -inf and the mask -1."""
+    import torch
+    import paper_1903_06934_amd as m
+    x = np.full((1, 3, F, F), -np.inf, np.float32)
+    x[0, 1] = np.nan
+    x[0, 2, 0, 0], x[0, 2, 1, 1] = np.nan, np.inf
+    got = [m.pool_fwd(dev(x), (F, F), st, 0, "max") for st in (2, 3)]
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    dy = torch.full((1, 3, 1, 1), float("inf"), device="cuda")
+    dx = [m.pool_bwd(dy, (F, F), (F, F), st, 0, "max", got[0][1]) for st in (2, 3)]
+    assert torch.equal(*dx)
+
+
 def test_max_pool_ties_take_the_first_element():
     """A constant plane: every window's argmax is its first element inside
     the image, in row-major order."""
