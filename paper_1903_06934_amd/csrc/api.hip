@@ -2300,10 +2300,8 @@ int wgrad_exec(const Geom &g, WgradPlan p, const float *x, const float *dy, floa
             return st;
         if (mark(tl_events.after, stream) != hipSuccess)
             return MICONV_ERR_LAUNCH;
-        if (db && (st = launch_status(launch_splitk_reduce(dy, N, K, K, db, 0, 0, stream))) !=
-                      MICONV_OK)
-            return st;
-        return MICONV_OK;
+        return launch_status(launch_splitk_reduce(SplitSum{}, SplitSum{dy, K, db ? K : 0, db, 0, 0},
+                                                  N, stream));
     }
     float *part = (float *)ws;
     float *db_part = (float *)((char *)ws + p.part_bytes);
@@ -2384,16 +2382,10 @@ int wgrad_exec(const Geom &g, WgradPlan p, const float *x, const float *dy, floa
     const int taps = p.xnb > 0 || p.bt ? 1 : R * S;
     const int ncol = g.Cg * R * S;
     const bool tap_order = p.halo_tw || is_tap_tile(p.tile);
-    if (p.via_part &&
-        (st = launch_status(launch_splitk_reduce(part, p.nsplit, (long long)K * ncol, K * ncol,
-                                                 dw, tap_order ? taps : 0,
-                                                 tap_order ? ncol / taps : 0, stream))) !=
-            MICONV_OK)
-        return st;
-    if (db && (st = launch_status(launch_splitk_reduce(db_part, p.nsplit, K, K, db, 0, 0,
-                                                       stream))) != MICONV_OK)
-        return st;
-    return MICONV_OK;
+    const SplitSum dws{part, (long long)K * ncol, p.via_part ? K * ncol : 0, dw,
+                       tap_order ? taps : 0, tap_order ? ncol / taps : 0};
+    return launch_status(
+        launch_splitk_reduce(dws, SplitSum{db_part, K, db ? K : 0, db, 0, 0}, p.nsplit, stream));
 }
 
 // Number, workspace, name and execution of candidate `index` of a pass.

@@ -329,9 +329,17 @@ hipError_t launch_transpose(const float *in, float *out, int rows, int cols, hip
 // Packed reduction-row length of the image GEMM's filter operand.
 inline int pad16(int k) { return (k + 15) & ~15; }
 // out[dst(i)] = sum over s < nsplit of part[s * stride + i] for i < count, in a
-// fixed order; dst = identity, or (tap_cg > 0) [k][tap][c] -> [k][c][tap].
-hipError_t launch_splitk_reduce(const float *part, int nsplit, long long stride, int count,
-                                float *out, int taps, int tap_cg, hipStream_t stream);
+// fixed order; dst = identity, or (tap_cg > 0) [k][tap][c] -> [k][c][tap].  Two
+// such sums over the same splits, either of which may be empty.
+struct SplitSum {
+    const float *part;
+    long long stride;
+    int count;
+    float *out;
+    int taps, tap_cg;
+};
+hipError_t launch_splitk_reduce(const SplitSum &a, const SplitSum &b, int nsplit,
+                                hipStream_t stream);
 // out[i] = sum over s < nsplit of part[s * stride + i] in a fixed order,
 // + bias[(i / hw) % K] if bias is given, for i < count.
 hipError_t launch_splitk_bias_reduce(const float *part, int nsplit, long long stride, int count,
