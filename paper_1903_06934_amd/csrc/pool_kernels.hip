@@ -213,7 +213,8 @@ __global__ __launch_bounds__(256) void pool_bwd_plane_kernel(const float *__rest
 // one before.  Here the planes arrive in 16-byte loads that are all requested
 // before the first is waited for, and a window's reads are unrolled; backward,
 // a thread computes a 2 x 2 block of dx from the one (F = 2) or four windows
-// over it.
+// over it.  96 planes of 55 x 55 at batch 128, 3 x 3, max: both passes 146.6 ->
+// 109.4 us (kernels 44.0 + 62.4), 4.0 TB/s of the 4.6-4.9 that a copy moves.
 // ---------------------------------------------------------------------------
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
