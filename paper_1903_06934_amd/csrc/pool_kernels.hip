@@ -387,8 +387,13 @@ unsigned pool_grid(uint32_t total)
     return b < 65536u ? b : 65536u;
 }
 
-// The stride-2 kernels' windows, and their planes a workgroup: enough for about
-// 1024 elements.
+// The stride-2 kernels' windows, on all planes that fit, and their planes a
+// workgroup: enough for about 1024 elements.  Measured (general / these, us,
+// forward and backward): 3 x 3 max on 13 x 13 planes, 256 at batch 128, 12.4 /
+// 12.4 and 20.2 / 14.1; 27 x 27 38.4 / 24.5 and 50.0 / 33.8; average with
+// padding on 56 x 56, 64 at batch 64, 20.0 / 15.6 and 46.4 / 19.7; 2 x 2 on
+// 104 x 104, 128 at batch 32, 116.6 / 47.3 and 72.7 / 59.7; 512 planes of 7 x 7
+// at batch 64 12.3 / 11.8 and 9.9 / 9.7.
 bool s2_applies(int R, int S, int stride, int pad)
 {
     return stride == 2 && R == S && (R == 2 || R == 3) && pad < R;
