@@ -19,6 +19,7 @@
 // instead of 100 for 2 x 2 outputs; to the products they are further channels.
 // The offsets are even so that the patches keep their alignment.
 #include "internal.h"
+#include "tile_offsets.h"
 
 namespace miconv {
 
@@ -27,8 +28,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 #define LDS_AS __attribute__((address_space(3)))
 
 namespace {
-
-constexpr uint32_t kOob = 0x80000000u;  // beyond any buffer of < 2^31 bytes
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes)
 {
@@ -400,7 +399,7 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
         const __amdgpu_buffer_rsrc_t rB = make_rsrc(c.bias, c.bias ? (uint32_t)(c.groups * M) * 4u : 0u);
         const uint32_t o0 = ((uint32_t)at.img * (uint32_t)c.out_img_stride +
                              (uint32_t)(g * M + m0) * (uint32_t)hw + (uint32_t)(p * Q + q)) * 4u;
-        const uint32_t o1 = p + 1 < P ? 0u : kOob;  // the tile's second row
+        const bool two_p = p + 1 < P, two_q = q + 1 < Q;
         float bv[2][4];
 #pragma unroll
         for (int b = 0; b < 2; b++)
@@ -428,21 +427,18 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
                     y[k] += bv[b][r];
                     zero = fmaf(y[k], 0.f, zero);
                 }
-                const uint32_t o = t < c.tiles && m0 + b * 16 + r < M
-                                       ? o0 + (uint32_t)((b * 16 + r) * hw) * 4u
-                                       : kOob;
-                const uint32_t oq = o | o1, Qb = (uint32_t)Q * 4u;
+                const TileOffsets o =
+                    tile_offsets(o0 + (uint32_t)((b * 16 + r) * hw) * 4u, (uint32_t)Q * 4u,
+                                 t < c.tiles && m0 + b * 16 + r < M, two_p, two_q);
                 if ((Q & 1) == 0) {
                     __builtin_amdgcn_raw_buffer_store_b64(
-                        u32x2{__float_as_uint(y[0]), __float_as_uint(y[1])}, rO, o, 0, 0);
+                        u32x2{__float_as_uint(y[0]), __float_as_uint(y[1])}, rO, o.at[0], 0, 0);
                     __builtin_amdgcn_raw_buffer_store_b64(
-                        u32x2{__float_as_uint(y[2]), __float_as_uint(y[3])}, rO, oq + Qb, 0, 0);
+                        u32x2{__float_as_uint(y[2]), __float_as_uint(y[3])}, rO, o.at[2], 0, 0);
                 } else {
-                    const uint32_t s = q + 1 < Q ? 0u : kOob;
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[0]), rO, o, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[1]), rO, (o | s) + 4, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[2]), rO, oq + Qb, 0, 0);
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[3]), rO, (oq | s) + Qb + 4, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < 4; k++)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(y[k]), rO, o.at[k], 0, 0);
                 }
             }
         // (Lanes outside the output hold sums of valid or zero operands.)

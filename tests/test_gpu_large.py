@@ -61,3 +61,50 @@ def test_explicit_plan_column_chunks():
     finally:
         m.plan_clear()
     _check_sampled(shape, d, y, dx, dw, db, "explicit")
+
+
+def test_fast_filtering_just_below_the_offset_limit():
+    """Outputs of 2^29 - 512 elements on a map of odd height and width, whose
+    last tiles have no second row or column: nothing that lies past them may
+    come back to the start of the buffer.  Forward, and the same layer's
+    mirror image backward; backward-weight reads the large tensor."""
+    import torch
+    import paper_1903_06934_amd as m
+    H, W, few, many = 1025, 1023, 32, 512
+    gen = torch.Generator(device="cuda").manual_seed(92)
+    small = torch.randn(1, few, H, W, device="cuda", generator=gen)
+    plane = np.arange(2 * W), np.arange((H - 2) * W, H * W)
+    rng = np.random.default_rng(92)
+    at = lambda c, i: c * H * W + i  # noqa: E731
+    idx = np.unique(np.concatenate([at(0, plane[0]), at(0, plane[1]), at(many - 1, plane[0]),
+                                    at(many - 1, plane[1]), rng.integers(0, many * H * W, 2048)]))
+
+    def fast(p, shape):
+        return [m.plan_name(p, shape, i).startswith("fast filtering")
+                for i in range(m.plan_count(p, shape))].index(True)
+
+    try:
+        shape = (1, few, H, W, many, 3, 3, 1, 1, 1)
+        w = torch.randn(many, few, 3, 3, device="cuda", generator=gen)
+        m.plan_set(m.PASS_FWD, shape, fast(m.PASS_FWD, shape))
+        got = host(m.conv_fwd(small, w, None, 1, 1, 1))
+        v, a = oracle.conv_fwd_at(shape, host(small), host(w), None, idx)
+        assert_within(got.ravel()[idx], v, a, "fwd")
+        del got
+
+        shape = (1, many, H, W, few, 3, 3, 1, 1, 1)
+        w = torch.randn(few, many, 3, 3, device="cuda", generator=gen)
+        m.plan_set(m.PASS_BWD_DATA, shape, fast(m.PASS_BWD_DATA, shape))
+        got = host(m.conv_bwd_data(small, w, (H, W), 1, 1, 1))
+        v, a = oracle.conv_bwd_data_at(shape, host(small), host(w), idx)
+        assert_within(got.ravel()[idx], v, a, "bwd_data")
+        del got
+
+        x = torch.randn(1, many, H, W, device="cuda", generator=gen)
+        m.plan_set(m.PASS_BWD_WEIGHT, shape, fast(m.PASS_BWD_WEIGHT, shape))
+        got = host(m.conv_bwd_weight(x, small, (3, 3), 1, 1, 1, with_bias=False)[0])
+        idx = np.unique(np.concatenate([np.arange(0, got.size, 3001), np.arange(got.size - 9, got.size)]))
+        v, a = oracle.conv_bwd_weight_at(shape, host(x), host(small), idx)
+        assert_within(got.ravel()[idx], v, a, "bwd_weight")
+    finally:
+        m.plan_clear()
