@@ -534,7 +534,9 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     }
 }
 
-// One output pixel directly: the sum over channels and taps in order.
+// One output pixel directly: the sum over channels and taps in order, the
+// padding's zeros multiplied too (by an infinite tap, to a NaN), as in the
+// direct plans.
 __device__ float wino_direct(const WinoArgs &a, int img, int oc, int p, int q)
 {
     const int g = oc / a.M, m = oc - g * a.M;
@@ -547,8 +549,8 @@ __device__ float wino_direct(const WinoArgs &a, int img, int oc, int p, int q)
         for (int r = 0; r < a.R; r++)
             for (int z = 0; z < a.R; z++) {
                 const int h = p + a.off + r, w = q + a.off + z, k = r * a.R + z;
-                if ((unsigned)h < (unsigned)a.src_h && (unsigned)w < (unsigned)a.src_w)
-                    s = fmaf(x[h * a.src_w + w], wt[a.flip ? taps - 1 - k : k], s);
+                const bool ok = (unsigned)h < (unsigned)a.src_h && (unsigned)w < (unsigned)a.src_w;
+                s = fmaf(ok ? x[h * a.src_w + w] : 0.f, wt[a.flip ? taps - 1 - k : k], s);
             }
     }
     return s + (a.bias ? a.bias[oc] : 0.f);
@@ -1147,8 +1149,8 @@ __global__ __launch_bounds__(256) void wino_wgrad_finish_kernel(const WinoWgArgs
         for (int img = 0; img < a.nimg; img++, x += a.x_img_words, dy += a.dy_img_words) {
             for (int pq = threadIdx.x; pq < a.PQ; pq += 256) {
                 const int p = pq / a.Q, h = p + r0, w = pq - p * a.Q + z0;
-                if ((unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W)
-                    v = fmaf(dy[pq], x[h * a.W + w], v);
+                const bool ok = (unsigned)h < (unsigned)a.H && (unsigned)w < (unsigned)a.W;
+                v = fmaf(dy[pq], ok ? x[h * a.W + w] : 0.f, v);
             }
             if (__syncthreads_or(v != v))
                 break;  // a NaN stays one

@@ -164,6 +164,62 @@ def test_infinities_and_nans_in_the_filter_gradient(shape):
     assert_within(a[:, 9][fin], ref[:, 9][fin], absum[:, 9][fin], "large gradients")
 
 
+def _mirrored(shape, w):
+    """Backward-data's problem as a forward one: its shape and filters."""
+    N, C, H, W, K, R, S, st, pad, G = shape
+    P, Q = oracle.out_size(H, R, st, pad), oracle.out_size(W, S, st, pad)
+    w = w.reshape(G, K // G, C // G, R, S).swapaxes(1, 2)[..., ::-1, ::-1]
+    return (N, K, P, Q, C, R, S, 1, R - 1 - pad, G), np.ascontiguousarray(w.reshape(C, K // G, R, S))
+
+
+def _assert_same_kinds(got, ref, absum, what):
+    """Infinities and NaNs where the reference has them, the others in the bar."""
+    assert np.array_equal(np.isnan(got), np.isnan(ref)), what
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)), what
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref)), what
+    fin = np.isfinite(ref)
+    assert 0 < fin.sum() < fin.size, what
+    assert_within(got[fin], ref[fin], absum[fin], what)
+
+
+@pytest.mark.parametrize("shape", [
+    (9, 64, 27, 29, 72, 3, 3, 1, 1, 1),     # odd map, a ragged block of tiles
+    (2, 48, 12, 14, 80, 3, 3, 1, 2, 2),     # groups, rows past the block's channels
+    (3, 32, 9, 10, 40, 5, 5, 1, 2, 1),      # 5 x 5
+    (2, 1040, 4, 4, 1104, 3, 3, 1, 1, 1),   # whole tiles of many channels
+], ids=lambda s: "x".join(map(str, s)))
+def test_infinities_and_nans_in_every_operand(shape):
+    """Infinities and NaNs spread over x, dy, the filters and the bias.  The
+    padding's zeros are operands like others: an infinite tap over them is a
+    NaN, as in the oracle's forward sums and in the direct plans of all passes
+    (backward-data as the forward problem that it mirrors)."""
+    import paper_1903_06934_amd as m
+    d = _inputs(shape, (76, 1))
+    rng = np.random.default_rng(76)
+    kinds = np.repeat(np.array([np.inf, -np.inf, np.nan], np.float32), 12)
+    for k in ("x", "dy"):
+        f = d[k][0].reshape(-1)
+        f[rng.choice(f.size, kinds.size, replace=False)] = kinds
+    d["dy"][0, 3, 0, 0] = np.inf  # under a tap that reads padding
+    w = d["w"].copy()
+    w[1, 2, 0, 0], w[3, 1, 2, 2] = np.inf, np.nan
+    d["b"][5], d["b"][7] = -np.inf, np.nan
+    t = {k: dev(v) for k, v in {**d, "w": w}.items()}
+    mirror, mw = _mirrored(shape, w)
+    for p, ref in ((m.PASS_FWD, oracle.conv_fwd(shape, d["x"], w, d["b"])),
+                   (m.PASS_BWD_DATA, oracle.conv_fwd(mirror, d["dy"], mw, None))):
+        m.plan_set(p, shape, _plan(p, shape, "fast"))
+        _assert_same_kinds(host(_run(p, shape, t)), *ref, f"pass {p}")
+    # Backward-weight: channels of x and dy without any stay finite.
+    x, dy = d["x"].copy(), d["dy"].copy()
+    x[:, 8:], dy[:, 8:] = _inputs(shape, (77, 1))["x"][:, 8:], _inputs(shape, (77, 1))["dy"][:, 8:]
+    m.plan_set(m.PASS_BWD_WEIGHT, shape, _plan(m.PASS_BWD_WEIGHT, shape, "fast"))
+    dw, db = m.conv_bwd_weight(dev(x), dev(dy), shape[5:7], 1, shape[8], shape[9])
+    dw_ref, adw, db_ref, adb = oracle.conv_bwd_weight(shape, x, dy)
+    _assert_same_kinds(host(dw), dw_ref, adw, "dw")
+    _assert_same_kinds(host(db), db_ref, adb, "db")
+
+
 def test_smaller_workspace_runs_the_direct_plan():
     """Where the workspace holds the direct plan but not the transformed
     filters, the rule runs the direct plan, bit for bit."""
