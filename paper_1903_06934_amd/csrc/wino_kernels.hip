@@ -21,6 +21,8 @@
 #include "internal.h"
 #include "tile_offsets.h"
 
+#include <algorithm>
+
 namespace miconv {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -195,6 +197,16 @@ __device__ __forceinline__ TileAt tile_at(const WinoArgs &a, int t)
     r.img = (int)fast_div((uint32_t)row, a.d_pt);
     r.ty = row - r.img * a.Pt;
     return r;
+}
+
+// The 2 x 2 outputs of output channel oc at a tile (zero where there are none).
+__device__ __forceinline__ f32x4 load_tile(const WinoArgs &a, const TileAt &at, int oc)
+{
+    const int p = 2 * at.ty, q = 2 * at.tx;
+    const float *const o = a.out + (long long)at.img * a.out_img_stride + (long long)oc * a.out_hw +
+                           (long long)p * a.Q + q;
+    const bool two_p = p + 1 < a.P, two_q = q + 1 < a.Q;
+    return f32x4{o[0], two_q ? o[1] : 0.f, two_p ? o[a.Q] : 0.f, two_p && two_q ? o[a.Q + 1] : 0.f};
 }
 
 // Stores the 2 x 2 outputs (bias added) of output channel oc at a tile.
@@ -534,26 +546,74 @@ __global__ __launch_bounds__(512, 2) void wino_gemm_kernel(const WinoArgs a)
     }
 }
 
-// One output pixel directly: the sum over channels and taps in order, the
-// padding's zeros multiplied too (by an infinite tap, to a NaN), as in the
+// Direct sums, over channels and taps in order, of the outputs in `bad` (bit k:
+// output (k >> 1, k & 1)) of the tile `at` of output channel oc.  All lanes of a
+// wave call it, on the same channel: a lane loads its tile's patch once for all
+// four outputs, and one word of the channel's filter for the others.  The
+// padding's zeros are multiplied too (by an infinite tap, to a NaN), as in the
 // direct plans.
-__device__ float wino_direct(const WinoArgs &a, int img, int oc, int p, int q)
+//
+// Waiting for the loads bounds it: a channel's are all requested together.  With
+// every output plus infinity a forward pass takes 3.3 ms on 64 -> 64 channels,
+// 112 x 112, batch 32 (one thread an output: 23; the direct plan: 0.25), 3.4 on 512
+// -> 512, 14 x 14 (11; 0.27); with NaNs, which end a sum, 0.25 and 0.15; with one
+// infinite input 0.21 (0.35) and 0.65 (4.3).
+template <int R>
+__device__ __forceinline__ void wino_direct(const WinoArgs &a, const TileAt &at, int oc, int bad, f32x4 &y)
 {
-    const int g = oc / a.M, m = oc - g * a.M;
-    float s = 0.f;
-    for (int c = 0; c < a.cin && s == s; c++) {  // (a NaN stays one)
-        const float *x = a.src + (size_t)img * a.src_img_words + (size_t)(g * a.cin + c) * a.src_hw;
-        const int taps = a.R * a.R;
-        const float *wt = a.flip ? a.w + ((size_t)(g * a.cin + c) * a.M + m) * taps
-                                 : a.w + ((size_t)(g * a.M + m) * a.cin + c) * taps;
-        for (int r = 0; r < a.R; r++)
-            for (int z = 0; z < a.R; z++) {
-                const int h = p + a.off + r, w = q + a.off + z, k = r * a.R + z;
-                const bool ok = (unsigned)h < (unsigned)a.src_h && (unsigned)w < (unsigned)a.src_w;
-                s = fmaf(ok ? x[h * a.src_w + w] : 0.f, wt[a.flip ? taps - 1 - k : k], s);
-            }
+    constexpr int D = R + 1, T = R * R;
+    const int lane = threadIdx.x & 63, g = oc / a.M, m = oc - g * a.M;
+    const int h0 = 2 * at.ty + a.off, w0 = 2 * at.tx + a.off;
+    const __amdgpu_buffer_rsrc_t rX = make_rsrc(a.src, a.src_bytes);
+    const __amdgpu_buffer_rsrc_t rW = make_rsrc(a.w, (uint32_t)(a.groups * a.M * a.cin) * (T * 4u));
+    // Backward-data: the filters of one input channel, taps mirrored.
+    const uint32_t tap = (uint32_t)(a.flip ? T - 1 - lane : lane) * 4u;
+    const uint32_t wbase = (uint32_t)(a.flip ? g * a.cin * a.M + m : oc * a.cin) * (T * 4u);
+    const uint32_t wstep = (a.flip ? a.M : 1) * (T * 4u), xstep = (uint32_t)a.src_hw * 4u;
+    const uint32_t base = ((uint32_t)at.img * a.src_img_words + (uint32_t)(g * a.cin) * (uint32_t)a.src_hw) * 4u;
+    uint32_t off[D * D];
+#pragma unroll
+    for (int e = 0; e < D * D; e++) {
+        const int h = h0 + e / D, q = w0 + e % D;
+        off[e] = (unsigned)h < (unsigned)a.src_h && (unsigned)q < (unsigned)a.src_w
+                     ? base + (uint32_t)(h * a.src_w + q) * 4u
+                     : kOob;
     }
-    return s + (a.bias ? a.bias[oc] : 0.f);
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    int live = bad;  // what is not a NaN yet (a NaN stays one)
+    for (int c = 0; c < a.cin && __builtin_amdgcn_ballot_w64(live != 0); c++) {
+        float d[D][D], wt[T];
+        const int xs = __builtin_amdgcn_readfirstlane((int)((uint32_t)c * xstep));
+        const float wl = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+            rW, lane < T ? (int)tap : (int)kOob,
+            __builtin_amdgcn_readfirstlane((int)(wbase + (uint32_t)c * wstep)), 0));
+#pragma unroll
+        for (int e = 0; e < D * D; e++)
+            d[e / D][e % D] = __uint_as_float(
+                __builtin_amdgcn_raw_buffer_load_b32(rX, (int)off[e], xs, 0));
+#pragma unroll
+        for (int t = 0; t < T; t++)
+            wt[t] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wl), t));
+#pragma unroll
+        for (int i = 0; i < D; i++)
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int r = i - (k >> 1);
+                if (r < 0 || r >= R)
+                    continue;
+#pragma unroll
+                for (int z = 0; z < R; z++)
+                    s[k] = fmaf(d[i][(k & 1) + z], wt[r * R + z], s[k]);
+            }
+        live = 0;
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            live |= s[k] == s[k] ? bad & (1 << k) : 0;
+    }
+    const float bv = a.bias ? a.bias[oc] : 0.f;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        y[k] = bad & (1 << k) ? s[k] + bv : y[k];
 }
 
 // The workgroup whose share holds the first stage of remaining tile r.
@@ -571,58 +631,57 @@ __device__ __forceinline__ int wino_first_share(const WinoWork &a, int r)
 // pixels of a tile, so that an infinity in x may become a NaN, or a finite
 // result overflow -- recomputes the output directly.  A block is 256 (channel,
 // tile) pairs of one cut output tile; then all blocks look through the output
-// if the GEMM raised the flag.
+// if the GEMM raised the flag, a wave for 64 tiles of a channel.
+template <int R>
 __global__ __launch_bounds__(256) void wino_finish_kernel(const WinoArgs a)
 {
-    if (a.rest) {
-        const int r = blockIdx.x >> 4, e = (blockIdx.x & 15) * 256 + threadIdx.x;
-        const int hi = (r + 1) * a.nstage;
-        int w = wino_first_share(a, r);
-        if (share(a, w + 1) < hi) {
-            f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
-            for (; w < a.nwg && share(a, w) < hi; w++) {
-                if (share(a, w) == share(a, w + 1))
-                    continue;
-                const f32x4 s = *(const f32x4 *)(a.slabs + (size_t)(w + r) * 16384 + e * 4);
-                y = f32x4{y[0] + s[0], y[1] + s[1], y[2] + s[2], y[3] + s[3]};
-            }
-            const int tile = a.rounds * a.nwg + r;
-            const int gm = tile / a.tblocks, tb = tile - gm * a.tblocks;
-            const int g = gm / a.mblocks, m = (gm - g * a.mblocks) * 64 + (e >> 6);
-            const int t = tb * 64 + (e & 63);
-            if (m < a.M && t < a.tiles) {
-                const TileAt at = tile_at(a, t);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int whole = a.rounds * a.nwg;  // output tiles before the remaining ones
+    const int rows = (whole + a.rest) * 64, place = (int)blockIdx.x * 4 + wave;
+    // First (cut = true) the wave's row of a cut tile, if it has one; then, on
+    // the flag, its share of all rows of the others.
+    bool cut = true;
+    for (int u = whole * 64 + place;; u += (int)gridDim.x * 4) {
+        const int tile = u >> 6, r = tile - whole, row = u & 63;
+        const int gm = tile / a.tblocks, tb = tile - gm * a.tblocks;
+        const int g = gm / a.mblocks, m = (gm - g * a.mblocks) * 64 + row;
+        const int t = tb * 64 + lane;
+        if (u < rows && m < a.M) {
+            const int hi = (r + 1) * a.nstage;
+            int w = r >= 0 ? wino_first_share(a, r) : 0;
+            if ((r >= 0 && share(a, w + 1) < hi) == cut) {
+                const TileAt at = tile_at(a, min(t, a.tiles - 1));
                 const int oc = g * a.M + m;
-                const float bv = a.bias ? a.bias[oc] : 0.f;
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    y[k] += bv;
-                    if (!is_finite(y[k]))
-                        y[k] = wino_direct(a, at.img, oc, 2 * at.ty + (k >> 1), 2 * at.tx + (k & 1));
+                f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (cut) {
+                    for (; w < a.nwg && share(a, w) < hi; w++) {
+                        if (share(a, w) == share(a, w + 1))
+                            continue;
+                        const f32x4 s = *(const f32x4 *)(a.slabs + (size_t)(w + r) * 16384 + (row * 64 + lane) * 4);
+                        y = f32x4{y[0] + s[0], y[1] + s[1], y[2] + s[2], y[3] + s[3]};
+                    }
+                    const float bv = a.bias ? a.bias[oc] : 0.f;
+                    y = f32x4{y[0] + bv, y[1] + bv, y[2] + bv, y[3] + bv};
+                } else {
+                    y = load_tile(a, at, oc);
                 }
-                store_tile(a, at, oc, y);
+                int bad = 0;
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+                    bad |= is_finite(y[k]) || t >= a.tiles ? 0 : 1 << k;
+                if (__builtin_amdgcn_ballot_w64(bad != 0))
+                    wino_direct<R>(cold_args<WinoArgs>(), at, oc, bad, y);
+                if (t < a.tiles && (cut || bad))
+                    store_tile(cold_args<WinoArgs>(), at, oc, y);
             }
         }
-    }
-    if (*a.flag) {
-        const long long total = (long long)a.nimg * a.out_img_stride;
-        for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total;
-             i += (long long)gridDim.x * 256) {
-            if (is_finite(a.out[i]))
-                continue;
-            const int img = (int)(i / a.out_img_stride);
-            const long long r = i - (long long)img * a.out_img_stride;
-            const int oc = (int)(r / a.out_hw), pq = (int)(r - (long long)oc * a.out_hw);
-            const int p = pq / a.Q, q = pq - p * a.Q;
-            // A cut output tile's pixels are another block's (above).
-            const int g = oc / a.M, t = (img * a.Pt + p / 2) * a.Qt + q / 2;
-            const int rest = (g * a.mblocks + (oc - g * a.M) / 64) * a.tblocks + t / 64 - a.rounds * a.nwg;
-            if (rest >= 0) {
-                const int w = wino_first_share(a, rest);
-                if (share(a, w + 1) < (rest + 1) * a.nstage)
-                    continue;
-            }
-            a.out[i] = wino_direct(a, img, oc, p, q);
+        if (cut) {
+            if (!__builtin_amdgcn_readfirstlane(*a.flag))
+                return;
+            cut = false;
+            u = place - (int)gridDim.x * 4;
+        } else if (u >= rows) {
+            return;
         }
     }
 }
@@ -1244,7 +1303,11 @@ hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stre
         return e;
     if (a.after && (e = hipEventRecord(a.after, stream)) != hipSuccess)
         return e;
-    wino_finish_kernel<<<dim3(p.rest ? (unsigned)p.rest * 16 : 64), 256, 0, stream>>>(a);
+    const dim3 blocks((unsigned)std::max(p.rest * 16, 8 * p.nwg));
+    if (a.R == 3)
+        wino_finish_kernel<3><<<blocks, 256, 0, stream>>>(a);
+    else
+        wino_finish_kernel<5><<<blocks, 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 

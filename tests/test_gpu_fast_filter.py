@@ -220,6 +220,42 @@ def test_infinities_and_nans_in_every_operand(shape):
     _assert_same_kinds(host(db), db_ref, adb, "db")
 
 
+def _ms(call):
+    import torch
+    call()
+    best = float("inf")
+    for _ in range(3):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        call()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("shape", [(32, 64, 112, 112, 64, 3, 3, 1, 1, 1),
+                                   (32, 512, 14, 14, 512, 3, 3, 1, 1, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_infinite_outputs_cost_a_bounded_time(shape):
+    """Every output plus infinity (none a NaN, where a sum may end early): the
+    direct sums take at most sixty times the direct plan's pass."""
+    import torch
+    import paper_1903_06934_amd as m
+    N, C, H, W, K = shape[:5]
+    t = {"x": torch.full((N, C, H, W), float("inf"), device="cuda"),
+         "w": torch.rand(K, C, 3, 3, device="cuda") + 0.1, "b": torch.zeros(K, device="cuda"),
+         "dy": torch.full((N, K, H, W), float("inf"), device="cuda")}
+    for p in (m.PASS_FWD, m.PASS_BWD_DATA):
+        ws = torch.empty(m.workspace_size(p, shape), dtype=torch.uint8, device="cuda")
+        ms = {}
+        for want in ("direct", "fast"):
+            m.plan_set(p, shape, _plan(p, shape, want))
+            assert torch.isposinf(_run(p, shape, t, ws=ws)).all()
+            ms[want] = _ms(lambda: _run(p, shape, t, ws=ws))
+        assert ms["fast"] < 60 * ms["direct"], (p, ms)
+
+
 def test_smaller_workspace_runs_the_direct_plan():
     """Where the workspace holds the direct plan but not the transformed
     filters, the rule runs the direct plan, bit for bit."""
