@@ -245,7 +245,7 @@ struct WinoWgArgs : WinoWork {
     hipEvent_t before, after;
     // Set by launch_wino_wgrad:
     int cw, cw_log, Pt, Qt, nstrip, kblocks, cblocks, parts;
-    FastDiv d_pt, d_strips, d_cblocks, d_kblocks, d_parts;
+    FastDiv d_pt, d_qt, d_strips, d_cblocks, d_kblocks, d_parts;
 };
 WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int R, int nimg, int P, int Q, int cus, int *cw);
 size_t wino_wgrad_slab_bytes(const WinoWork &w);

@@ -246,7 +246,11 @@ def test_infinite_outputs_cost_a_bounded_time(shape):
     t = {"x": torch.full((N, C, H, W), float("inf"), device="cuda"),
          "w": torch.rand(K, C, 3, 3, device="cuda") + 0.1, "b": torch.zeros(K, device="cuda"),
          "dy": torch.full((N, K, H, W), float("inf"), device="cuda")}
-    for p in (m.PASS_FWD, m.PASS_BWD_DATA):
+    for p in (m.PASS_FWD, m.PASS_BWD_DATA, m.PASS_BWD_WEIGHT):
+        if p == m.PASS_BWD_WEIGHT:
+            t["x"].uniform_(0.1, 1)  # (an infinity times the padding would be a NaN)
+            t["dy"][:, :, 1:-1, 1:-1] = float("inf")
+            t["dy"][:, :, ::H - 1], t["dy"][..., ::W - 1] = 0, 0
         ws = torch.empty(m.workspace_size(p, shape), dtype=torch.uint8, device="cuda")
         ms = {}
         for want in ("direct", "fast"):
