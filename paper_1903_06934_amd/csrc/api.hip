@@ -82,7 +82,8 @@ int make_geom(int N, int C, int H, int W, int K, int R, int S, int stride, int p
     if (H > 32767 || W > 32767 || R > 32767 || S > 32767 || pad > 32767)
         return MICONV_ERR_SHAPE;
     // Groups are folded with the tiles and splits into the 1-D grid; keeping
-    // them below 2^16 keeps that product far from the grid limit.
+    // them below 2^16 keeps that product within the grid limit (but see
+    // wgrad_wino_applies).
     if (group > 65535)
         return MICONV_ERR_SHAPE;
     int P = out_extent(H, R, stride, pad), Q = out_extent(W, S, stride, pad);
@@ -1281,10 +1282,12 @@ WgradPlan wgrad_halo_plan(const Geom &g, int tw, int scale = 0, int ct = 1, int 
 }
 
 // Fast filtering of backward-weight (wino_wgrad_kernel): the same layers,
-// any channel counts, all images in one launch.
+// any channel counts that keep its last launch below 2^32 threads (58052 groups
+// of 3 x 3 filters, 14513 of 5 x 5), all images in one launch.
 bool wgrad_wino_applies(const Geom &g)
 {
-    return halo_filter(g) && images_per_launch(g) >= g.N;
+    return halo_filter(g) && images_per_launch(g) >= g.N &&
+           wino_wgrad_finish_threads(g.Kg, g.Cg, g.G, g.R) < 1LL << 32;
 }
 
 size_t wgrad_wino_ws(const Geom &g)

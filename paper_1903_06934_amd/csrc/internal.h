@@ -249,6 +249,7 @@ struct WinoWgArgs : WinoWork {
 };
 WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int R, int nimg, int P, int Q, int cus, int *cw);
 size_t wino_wgrad_slab_bytes(const WinoWork &w);
+long long wino_wgrad_finish_threads(int Kg, int Cg, int groups, int R);
 hipError_t launch_wino_wgrad(WinoWgArgs a, const WinoWork &p, int cw, hipStream_t stream);
 
 // Image-GEMM tile shapes (BM x BN; 4 waves, 3 for 48x64).

@@ -1366,6 +1366,17 @@ hipError_t launch_wino(WinoArgs a, const WinoWork &p, float *U, hipStream_t stre
     return hipGetLastError();
 }
 
+// Output tiles of backward-weight, and the threads of its last launch.
+static long long wino_wgrad_tiles(int Kg, int Cg, int groups, int R)
+{
+    return (long long)groups * ((Kg + 63) / 64) * ((Cg + 63) / 64) * wino_parts(R) * wino_parts(R);
+}
+
+long long wino_wgrad_finish_threads(int Kg, int Cg, int groups, int R)
+{
+    return wino_wgrad_tiles(Kg, Cg, groups, R) * WG_BLOCKS * 256;
+}
+
 // Columns of a stage's eight tiles: 8, or 4 of two or 2 of four images where
 // that leaves fewer lanes idle (28 x 28 maps, 14 tiles wide, 512 channels:
 // 0.521 ms with 2 columns, 0.560 with 8; one column of eight images was 17-28 %
@@ -1379,8 +1390,7 @@ WinoWork wino_wgrad_plan(int Kg, int Cg, int groups, int R, int nimg, int P, int
     for (int c : {4, 2})
         if (strips(c) < strips(*cw))
             *cw = c;
-    return wino_work((long long)groups * ((Kg + 63) / 64) * ((Cg + 63) / 64) * wino_parts(R) * wino_parts(R),
-                     (int)(strips(*cw) * Pt), cus, 8);
+    return wino_work(wino_wgrad_tiles(Kg, Cg, groups, R), (int)(strips(*cw) * Pt), cus, 8);
 }
 
 size_t wino_wgrad_slab_bytes(const WinoWork &w)

@@ -227,3 +227,15 @@ def test_padded_one_by_one_is_not_an_inner_product(shape):
             assert "batch-transposed" not in m.plan_name(p, shape, i)
     unpadded = shape[:8] + (0, 1)
     assert "batch-transposed" in m.plan_name(m.PASS_FWD, unpadded[:7] + (1, 0, 1), 0)
+
+
+@pytest.mark.parametrize("F,G,offered", [(3, 58052, True), (3, 58054, False), (3, 65535, False),
+                                         (5, 14513, True), (5, 14514, False), (5, 65535, False)])
+def test_fast_backward_weight_within_the_grid_limit(F, G, offered):
+    """Its last launch has 289 blocks of 256 threads an output tile (four tiles
+    a group for 5x5), and a launch at most 2^32 - 1 threads: layers of more
+    groups do not offer it, which would fail where conv_tune times it."""
+    shape = (1, G, 4, 4, G, F, F, 1, F // 2, G)
+    names = [m.plan_name(m.PASS_BWD_WEIGHT, shape, i)
+             for i in range(m.plan_count(m.PASS_BWD_WEIGHT, shape))]
+    assert any(n.startswith("fast filtering") for n in names) == offered
