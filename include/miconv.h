@@ -191,12 +191,22 @@ int conv_set_timing_events(hipEvent_t before, hipEvent_t after);
  * filtering (F(2x2, 3x3), backward-weight F(3x3, 2x2), 5 x 5 filters in four
  * 3 x 3 parts: 16 multiplications instead of 36, or 64 instead of 100, for
  * 2 x 2 outputs and a channel), in fp32 throughout.  Its results differ by
- * rounding only: less than a direct plan's on dense data; where a layer's
- * filters or inputs cancel or skip products exactly (a filter with a single
- * tap, say), by roundings of the size of the neighbouring products.  Outputs
- * that are infinite or NaN are recomputed as direct sums, padding included:
- * where all are, a pass takes 1 to 4 times a direct plan's with NaNs, up to 15
- * times (backward-weight 35 times) with infinities alone.  Where it applies
+ * rounding only: less than a direct plan's on dense data, where both are within
+ * 1e-4 of the sum of an element's |products|.  The transforms mix the products
+ * of a 2 x 2 tile.  Where these differ widely or an element's own are all zero
+ * (filters with few taps, an outlying pixel, zero borders), that bound does not
+ * hold, and an element is off by roundings of its tile's products: by at most
+ * 1e-4 of the sum, over the channels, of (the filter's |taps|, summed) times
+ * (the |pixels| of the (R + 1) x (R + 1) patch under the tile, summed), plus
+ * |bias|; backward-weight, over the 2 x 2 tiles of dy, of (the tile's |pixels|)
+ * times (the |pixels| of the patch of x under it).  It is exactly 0 where that
+ * sum is 0.  The direct plans keep the bound of the element's own products;
+ * conv_plan_set selects one.
+ * Outputs that are infinite or NaN are recomputed as direct sums, padding
+ * included: where all are, a pass takes 1 to 4 times a direct plan's with NaNs,
+ * up to 15 times (backward-weight 35 times) with infinities alone.
+ * It applies to tensors of fewer than 2^29 elements, forward and backward-data
+ * with a multiple of 8 source channels a group.  Where it applies
  * the list offers it as "fast filtering ...".  The rule uses it where it
  * measured faster and the workspace holds it (conv_workspace_size always does);
  * candidate 0 keeps the name and the workspace of the rule's direct plan, which

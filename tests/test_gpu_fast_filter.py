@@ -333,3 +333,94 @@ def test_captured_graph_replays():
         got = host(y)
         want = host(m.conv_fwd(t["x"], t["w"], t["b"], 1, 1, 1))
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+def _patch_sums(a, R, pad, P, Q):
+    """Sum of |a| over the (R + 1) x (R + 1) patch under each 2 x 2 output tile:
+    [N, C, tile rows, tile columns]."""
+    Pt, Qt = (P + 1) // 2, (Q + 1) // 2
+    N, C, H, W = a.shape
+    big = np.zeros((N, C, 2 * Pt + R - 1 + H, 2 * Qt + R - 1 + W))
+    big[:, :, pad:pad + H, pad:pad + W] = np.abs(a.astype(np.float64))
+    return sum(big[:, :, i:i + 2 * Pt:2, j:j + 2 * Qt:2] for i in range(R + 1) for j in range(R + 1))
+
+
+def _out_bound(shape, x, w, b):
+    """Scale of fast filtering's rounding, per output: over the channels, every
+    tap of the filter by every pixel of its tile's patch, plus |bias|."""
+    N, C, H, W, K, R, S, st, pad, G = shape
+    P, Q = oracle.out_size(H, R, st, pad), oracle.out_size(W, S, st, pad)
+    xs, ws = _patch_sums(x, R, pad, P, Q), np.abs(w.astype(np.float64)).sum((2, 3))
+    t = np.einsum("ngcyx,gkc->ngkyx", xs.reshape(N, G, C // G, *xs.shape[2:]),
+                  ws.reshape(G, K // G, C // G)).reshape(N, K, *xs.shape[2:])
+    t = t.repeat(2, 2).repeat(2, 3)[:, :, :P, :Q]
+    return t if b is None else t + np.abs(b.astype(np.float64)).reshape(1, K, 1, 1)
+
+
+def _grad_bound(shape, x, dy):
+    """The same of a filter gradient: over the 2 x 2 tiles of dy, every pixel of
+    the tile by every pixel of the patch of x under it."""
+    N, C, H, W, K, R, S, st, pad, G = shape
+    P, Q = dy.shape[2:]
+    xs, ys = _patch_sums(x, R, pad, P, Q), _patch_sums(dy, 1, 0, P, Q)
+    t = np.einsum("ngkyx,ngcyx->gkc", ys.reshape(N, G, K // G, *ys.shape[2:]),
+                  xs.reshape(N, G, C // G, *xs.shape[2:])).reshape(K, C // G, 1, 1)
+    return np.broadcast_to(t, (K, C // G, R, S))
+
+
+def _uneven(shape, kind, seed):
+    """Inputs whose products differ widely inside a tile's patch."""
+    N, C, H, W, K, R, S, st, pad, G = shape
+    d = _inputs(shape, seed)
+    rng = np.random.default_rng(seed)
+    d["b"][:] = 0
+    d["x"] = np.maximum(d["x"], 0)
+    if kind == "identity":  # one tap a filter, one pixel a plane of dy
+        d["w"][:] = 0
+        d["w"][np.arange(K), np.arange(K) % (C // G), R // 2, S // 2] = 1
+        keep = np.zeros(d["dy"].shape[:2] + (d["dy"][0, 0].size,), np.float32)
+        np.put_along_axis(keep, rng.integers(0, keep.shape[2], keep.shape[:2] + (1,)), 1, 2)
+        d["dy"] *= keep.reshape(d["dy"].shape)
+    elif kind == "pruned":
+        for k in ("w", "dy"):
+            d[k] *= rng.random(d[k].shape) < 0.02
+    elif kind == "outlier":
+        d["x"][0, 1, H // 2, W // 2] = 5e5
+        d["dy"][0, 1, H // 2, W // 2] = -5e5
+    else:  # images smaller than their map
+        d["x"][..., W // 2:], d["dy"][..., W // 2:] = 0, 0
+        d["x"][:, :, H // 2 + 1:], d["dy"][:, :, H // 2 + 1:] = 0, 0
+    return d
+
+
+@pytest.mark.parametrize("kind", ["identity", "pruned", "outlier", "zero border"])
+@pytest.mark.parametrize("shape", [(2, 64, 14, 14, 64, 3, 3, 1, 1, 1),
+                                   (2, 48, 9, 11, 96, 3, 3, 1, 1, 2),
+                                   (1, 64, 10, 13, 48, 5, 5, 1, 2, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_rounding_on_uneven_data(shape, kind):
+    """Where products differ widely inside a tile's patch, or are zero, fast
+    filtering is off by roundings of the patch's products, which the transforms
+    mix, and exact where those are all zero; the direct plans keep the bar of
+    their own products.  Limit: n accumulated products and at most 32 further
+    roundings (transforms, slabs, bias), each of at most 2^-24 of a partial sum;
+    mixing counts a tap's product with a pixel at most twice an axis."""
+    import paper_1903_06934_amd as m
+    d = _uneven(shape, kind, (78, 1))
+    N, C, H, W, K, R, S, st, pad, G = shape
+    t = {k: dev(v) for k, v in d.items()}
+    mirror, mw = _mirrored(shape, d["w"])
+    parts = ((R - 1) // 2) ** 2
+    tiles = N * -(-d["dy"].shape[2] // 2) * -(-d["dy"].shape[3] // 2)
+    for p, n, ref, bound in (
+            (m.PASS_FWD, C // G * parts, oracle.conv_fwd(shape, d["x"], d["w"], d["b"]),
+             _out_bound(shape, d["x"], d["w"], d["b"])),
+            (m.PASS_BWD_DATA, K // G * parts, oracle.conv_bwd_data(shape, d["dy"], d["w"]),
+             _out_bound(mirror, d["dy"], mw, None)),
+            (m.PASS_BWD_WEIGHT, tiles, oracle.conv_bwd_weight(shape, d["x"], d["dy"])[:2],
+             _grad_bound(shape, d["x"], d["dy"]))):
+        m.plan_set(p, shape, _plan(p, shape, "fast"))
+        assert_within(host(_run(p, shape, t)), ref[0], bound, f"pass {p}, fast",
+                      rel=4 * (n + 32) * 2.0**-24)
+        m.plan_set(p, shape, _plan(p, shape, "direct"))
+        assert_within(host(_run(p, shape, t)), *ref, f"pass {p}, direct")
