@@ -555,8 +555,8 @@ bool halo_rule(int M, int cin, int nimg, int Pout, int Qout, int src_w, int R, i
 
 // ------------------------------------------------------------ fast filtering
 // Stride-1 3 x 3 layers, and 5 x 5 ones in four 3 x 3 parts, by F(2x2, 3x3)
-// (wino_kernels.hip): M rows over cin
-// source channels per group, all images in one launch.
+// (wino_kernels.hip): M rows over cin source channels per group, all images in
+// one launch (a batch that takes several keeps the direct plans).
 bool wino_applies(const Geom &g, int M, int cin)
 {
     return halo_filter(g) && cin % 8 == 0 && images_per_launch(g) >= g.N &&
@@ -570,8 +570,9 @@ bool wino_applies(const Geom &g, int M, int cin)
 // MI355X (direct / fast time, forward and backward-data alike): 64 channels on
 // 56 x 56 maps 0.83 at 784 stages, 1.05 at 1568, 1.35 at 3136; 32 to 64
 // channels 0.85 at 392, 1.02-1.19 at 784-1568; 96 to 128 channels on 28 x 28
-// 0.97 at 1176, 1.24 at 2352; with 128 channels and more 1.1-1.8 from 32
-// stages on (512 on 7 x 7: 1.0-1.1); VGG-16 conv1_2 ... conv5_3 at batch 32
+// 0.97 at 1176, 1.24 at 2352; with 128 channels and more 1.3-3.7 at 16 to 128
+// stages, the fewest there are, one image of 2 x 2 to 14 x 14 (512 channels,
+// 512 stages: 1.0-1.1), 1.1-1.8 above; VGG-16 conv1_2 ... conv5_3 at batch 32
 // 1.6-1.9, ResNet-50's 3 x 3 layers at batch 64 1.4-1.7, AlexNet conv3-conv5
 // 1.4-1.5.  Fewer than 32 rows leave most of a 64-row tile idle; with fewer
 // than 32 channels the transforms' rounding is no longer small beside the
@@ -579,8 +580,9 @@ bool wino_applies(const Geom &g, int M, int cin)
 // 5 x 5 layers (16 multiplications of 25, so less to gain) take it from 64
 // channels and 48 rows on, or 48 channels and 12 stages a CU: AlexNet conv2 (48
 // to 128 channels a group, 27 x 27, batch 128) 1.20 forward, 1.25 backward-data;
-// 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.2-1.9; 48 to 128 on 14 x 14
-// (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.
+// 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.2-1.9; 64 to 128 channels on one
+// or four images of 4 x 4 to 28 x 28 2.2-3.1 (128 -> 128 1.0-1.2); 48 to 128 on 14 x
+// 14 (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.
 bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout)
 {
     if (cin < 32 || M < 32 || !wino_applies(g, M, cin))
