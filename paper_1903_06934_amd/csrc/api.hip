@@ -577,24 +577,35 @@ bool wino_applies(const Geom &g, int M, int cin)
 // 1.4-1.5.  Fewer than 32 rows leave most of a 64-row tile idle; with fewer
 // than 32 channels the transforms' rounding is no longer small beside the
 // sums' (error against 64 bits at 16 channels: equal to the direct plans').
+// With 65 rows or 32 half of a tile is empty: 0.86-1.8 with 3 to 3.7 full tiles'
+// worth of stages a CU, 0.98-1.9 from 4 on; 32 rows of up to 64 channels 0.86-1.1
+// below 8, 1.1-1.8 from there.
 // 5 x 5 layers (16 multiplications of 25, so less to gain) take it from 64
 // channels and 48 rows on, or 48 channels and 12 stages a CU: AlexNet conv2 (48
 // to 128 channels a group, 27 x 27, batch 128) 1.20 forward, 1.25 backward-data;
 // 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.2-1.9; 64 to 128 channels on one
 // or four images of 4 x 4 to 28 x 28 2.2-3.1 (128 -> 128 1.0-1.2); 48 to 128 on 14 x
-// 14 (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.
-bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout)
+// 14 (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.  Not where few
+// tiles of a long reduction are cut in 16 parts and more, which its last launch
+// adds one after another, and the direct image GEMM is split as well: 0.64-1.4
+// (464 -> 48 channels on 8 x 47, batch 6: 34 / 53 us), with fewer parts 0.89-1.9
+// (five of 1600 layers below 0.97).
+bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout, const ImgPlan &direct)
 {
     if (cin < 32 || M < 32 || !wino_applies(g, M, cin))
         return false;
     const long long tiles = (long long)g.N * ((Pout + 1) / 2) * ((Qout + 1) / 2);
-    if (g.R == 5)
-        return M >= 48 && cin >= 48 &&
-               (cin >= 64 || (long long)g.G * ((M + 63) / 64) * ((tiles + 63) / 64) * (cin / 2) >=
-                                 12 * num_cus());
+    const long long row = (long long)g.G * ((tiles + 63) / 64) * (cin / 8);  // stages a 64-row block
+    if (g.R == 5) {
+        if (M < 48 || cin < 48 || (cin < 64 && row * 4 * ((M + 63) / 64) < 12 * num_cus()))
+            return false;
+        const WinoWork w = wino_plan(M, cin, g.G, g.R, g.N, Pout, Qout, num_cus());
+        return direct.halo >= 0 || direct.nsplit == 1 || w.rounds > 0 || w.nwg < 16 * w.rest;
+    }
     if (cin >= 128 && M >= 64)
         return true;
-    return (long long)g.G * ((M + 63) / 64) * ((tiles + 63) / 64) * (cin / 8) >= 6 * num_cus();
+    return row * ((M + 63) / 64) >= 6 * num_cus() &&
+           row * M >= (M < 48 && cin <= 64 ? 8 : 4) * 64 * num_cus();
 }
 
 // The flag, the transformed filters, the slabs of cut tiles.
@@ -770,7 +781,7 @@ ImgPlan fwd_rule(const Geom &g)
         !halo_rule(g.Kg, g.Cg, g.N < nb ? g.N : nb, g.P, g.Q, g.W, g.R, g.G, &h))
         h = img_rule(g.Kg, (long long)(g.N < nb ? g.N : nb) * g.P * g.Q, g.Cg * g.R * g.S, g.G,
                      nb >= g.N);
-    if (wino_rule(g, g.Kg, g.Cg, g.P, g.Q))
+    if (wino_rule(g, g.Kg, g.Cg, g.P, g.Q, h))
         h.wino = WINO_RULE;
     return h;
 }
@@ -982,7 +993,7 @@ BwdPlan bwd_rule(const Geom &g)
     } else {
         p.img = ImgPlan{-1, 1, 0};
     }
-    if (!p.bt && !p.blocked && wino_rule(g, g.Cg, g.Kg, g.H, g.W))
+    if (!p.bt && !p.blocked && wino_rule(g, g.Cg, g.Kg, g.H, g.W, p.img))
         p.img.wino = WINO_RULE;
     return p;
 }
@@ -1300,28 +1311,40 @@ size_t wgrad_wino_ws(const Geom &g)
 }
 
 // The built-in rule's use of it: where its 64 x 64 tiles are mostly real, a tile
-// has at least 32 stages (of eight 2 x 2 tiles of dy) to reduce and there are at
-// least 6 stages a CU.  Measured on the MI355X (direct / fast time): VGG-16
+// has at least 32 stages (of eight 2 x 2 tiles of dy) to reduce, and the layer's
+// products fill at least 7 stages a CU, 11 on maps of odd width (whose loads are
+// of single words).  Measured on the MI355X (direct / fast time): VGG-16
 // conv1_2 ... conv4_3 at batch 32 1.6-1.9, conv5_x 1.5; ResNet-50's 3 x 3
-// layers at batch 64 1.2-1.5; AlexNet conv3-conv5 1.4-1.5; 64 to 256 channels
-// at batch 16 1.06-1.16 (1568 stages); 512 channels on 14 x 14 maps 0.84 at
-// batch 4 (24 stages a tile), 1.27 at batch 16; half-empty tiles (32 -> 64
-// channels) 0.93-1.0, 16 -> 16 0.6-0.8.  5 x 5 layers on maps of an even width
-// with at least 16 stages a CU (the four parts of the filter count as tiles):
-// 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.24-1.5; AlexNet conv2 (27 x 27)
-// 0.89, 96 -> 128 on 8 x 8 (8 stages a CU) 0.91.
+// layers at batch 64 1.2-1.5; AlexNet conv3-conv5 1.4-1.5; 512 channels on 14 x
+// 14 maps 0.84 at batch 4 (24 stages a tile), 1.27 at batch 16; half-empty tiles
+// (32 -> 64 channels) 0.93-1.0, 16 -> 16 0.6-0.8.  1300 layers of 32 to 512 channels
+// a group, batch 1 to 128, maps of 4 to 112: 0.64-1.3 with fewer stages' worth
+// (the stages are then mostly padding, and the slabs' sums not small beside
+// them), else 0.92-2.4, three below 0.97.  Where a stage's two columns of four images (a strided
+// load each) meet tiles that are a quarter empty, which the direct 48-channel
+// tiles are not (odd widths), or a single block of fewer than 64 (even ones):
+// 0.86-1.3 (48 -> 64 channels on 53 x 34, batch 37: 50 / 59 us).
+// 5 x 5 layers (the four parts of the filter count as tiles) on maps of an even
+// width where the products fill three quarters of a part's stages and 18 a CU:
+// 1.05-1.5 (one of 60 0.87); AlexNet conv2 (27 x 27) 0.89, fuller or longer ones 0.77-1.2,
+// else 0.34-1.2 (384 -> 288 channels on 10 x 6, batch 74: 92 / 159 us).
 bool wgrad_wino_rule(const Geom &g)
 {
     if (!wgrad_wino_applies(g))
         return false;
     int cw;
     const WinoWork w = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, g.N, g.P, g.Q, num_cus(), &cw);
-    const long long kb = (g.Kg + 63) / 64, cb = (g.Cg + 63) / 64;
-    if (10LL * g.Kg * g.Cg < 6 * 4096 * kb * cb || w.nstage < 32)
+    const long long kb = (g.Kg + 63) / 64, cb = (g.Cg + 63) / 64, full = 4096 * kb * cb;
+    const long long channels = (long long)g.Kg * g.Cg;
+    if (10 * channels < 6 * full || w.nstage < 32)
         return false;
+    // The products in stages of 64 x 64 channels and 32 pixels.
+    const long long real = channels * g.G * ((long long)g.N * g.P * g.Q) / (4096 * 32);
     if (g.R == 5)
-        return g.W % 2 == 0 && 4 * kb * cb * g.G * w.nstage >= 16 * num_cus();
-    return kb * cb * g.G * w.nstage >= 6 * num_cus();
+        return g.W % 2 == 0 && real >= 18 * num_cus() && 4 * real >= 3 * (kb * cb * g.G * w.nstage);
+    if (real < (g.W % 2 ? 11 : 7) * num_cus())
+        return false;
+    return cw > 2 || (g.W % 2 ? 4 * channels > 3 * full : g.Kg >= 64 && g.Cg >= 64);
 }
 
 WgradPlan wgrad_direct_rule(const Geom &g)

@@ -239,3 +239,37 @@ def test_fast_backward_weight_within_the_grid_limit(F, G, offered):
     names = [m.plan_name(m.PASS_BWD_WEIGHT, shape, i)
              for i in range(m.plan_count(m.PASS_BWD_WEIGHT, shape))]
     assert any(n.startswith("fast filtering") for n in names) == offered
+
+
+@pytest.mark.parametrize("p,shape,fast", [
+    # Forward and backward-data: tiles of 32 rows, few a CU; 5x5 filters on few
+    # tiles, each cut in many parts.
+    (m.PASS_FWD, (88, 48, 30, 30, 32, 3, 3, 1, 1, 1), False),
+    (m.PASS_FWD, (5, 192, 79, 79, 32, 3, 3, 1, 0, 1), True),
+    (m.PASS_FWD, (1, 128, 2, 2, 64, 3, 3, 1, 1, 1), True),
+    (m.PASS_FWD, (6, 464, 8, 47, 48, 5, 5, 1, 0, 1), False),
+    (m.PASS_FWD, (2, 464, 8, 8, 317, 5, 5, 1, 2, 1), False),
+    (m.PASS_BWD_DATA, (1, 96, 6, 6, 704, 5, 5, 1, 2, 2), False),
+    (m.PASS_FWD, (1, 64, 14, 14, 64, 5, 5, 1, 2, 1), True),
+    (m.PASS_FWD, (1, 128, 14, 14, 128, 5, 5, 1, 2, 1), False),
+    (m.PASS_FWD, (4, 128, 14, 14, 128, 5, 5, 1, 2, 1), False),
+    (m.PASS_FWD, (16, 128, 14, 14, 128, 5, 5, 1, 2, 1), True),
+    # Backward-weight: stages that are mostly padding, few products a CU, two
+    # columns a stage on partly empty tiles; 5x5 filters.
+    (m.PASS_BWD_WEIGHT, (1, 457, 77, 6, 416, 3, 3, 1, 1, 1), False),
+    (m.PASS_BWD_WEIGHT, (9, 96, 25, 10, 896, 3, 3, 1, 1, 2), False),
+    (m.PASS_BWD_WEIGHT, (3, 96, 85, 85, 64, 3, 3, 1, 1, 1), False),
+    (m.PASS_BWD_WEIGHT, (37, 48, 53, 34, 64, 3, 3, 1, 1, 1), False),
+    (m.PASS_BWD_WEIGHT, (27, 48, 101, 101, 256, 3, 3, 1, 0, 1), False),
+    (m.PASS_BWD_WEIGHT, (64, 96, 28, 28, 128, 3, 3, 1, 1, 1), True),
+    (m.PASS_BWD_WEIGHT, (128, 384, 13, 13, 384, 3, 3, 1, 1, 2), True),
+    (m.PASS_BWD_WEIGHT, (74, 288, 10, 6, 384, 5, 5, 1, 0, 1), False),
+    (m.PASS_BWD_WEIGHT, (4, 96, 94, 94, 256, 5, 5, 1, 0, 2), False),
+    (m.PASS_BWD_WEIGHT, (32, 64, 56, 56, 192, 5, 5, 1, 2, 1), True),
+])
+def test_rule_uses_fast_filtering_where_it_is_faster(p, shape, fast):
+    """Layers on either side of the rules' lines, timed with both plans (the rule
+    that uses fast filtering lists its direct plan separately)."""
+    names = [m.plan_name(p, shape, i) for i in range(m.plan_count(p, shape))]
+    assert any(n.startswith("fast filtering") for n in names)
+    assert any(n.endswith("products summed directly") for n in names) == fast
