@@ -387,16 +387,23 @@ unsigned pool_grid(uint32_t total)
     return b < 65536u ? b : 65536u;
 }
 
-// The stride-2 kernels' windows, on all planes that fit, and their planes a
+// The stride-2 kernels' windows, on planes that fit, and their planes a
 // workgroup: enough for about 1024 elements.  Measured (general / these, us,
 // forward and backward): 3 x 3 max on 13 x 13 planes, 256 at batch 128, 12.4 /
 // 12.4 and 20.2 / 14.1; 27 x 27 38.4 / 24.5 and 50.0 / 33.8; average with
 // padding on 56 x 56, 64 at batch 64, 20.0 / 15.6 and 46.4 / 19.7; 2 x 2 on
 // 104 x 104, 128 at batch 32, 116.6 / 47.3 and 72.7 / 59.7; 512 planes of 7 x 7
-// at batch 64 12.3 / 11.8 and 9.9 / 9.7.
-bool s2_applies(int R, int S, int stride, int pad)
+// at batch 64 12.3 / 11.8 and 9.9 / 9.7.  Not on small planes (below kPlaneMin) of
+// fewer than kS2Min elements, which are few workgroups and so wait for the staging
+// (3-4 us either way): backward 3.0 / 3.6 on 58 planes of 11 x 11, 3.2 / 4.3 on 812
+// of 4 x 4, forward 2-8 % more; a tie or better from kS2Min on.  Forward 3 x 3
+// windows all inside the image gain there too (5-19 %).
+constexpr long long kS2Min = 1 << 19;
+bool s2_applies(int R, int S, int stride, int pad, int H, int W, uint32_t planes, bool inside)
 {
-    return stride == 2 && R == S && (R == 2 || R == 3) && pad < R;
+    return stride == 2 && R == S && (R == 2 || R == 3) && pad < R &&
+           ((long long)H * W >= kPlaneMin || (long long)H * W * planes >= kS2Min ||
+            (inside && R == 3));
 }
 uint32_t s2_planes(int H, int W, uint32_t planes)
 {
@@ -413,9 +420,9 @@ hipError_t launch_pool_fwd(bool max_mode, const float *x, float *y, int *mask, i
     const uint32_t total = (uint32_t)((long long)N * C * P * Q);
     const uint32_t planes = (uint32_t)((long long)N * C);
     const size_t lds = (size_t)H * W * sizeof(float);
-    if (s2_applies(R, S, stride, pad) && lds <= kPlaneLds) {
+    const bool full = pad == 0 && 2 * (P - 1) + R <= H && 2 * (Q - 1) + R <= W;
+    if (s2_applies(R, S, stride, pad, H, W, planes, full) && lds <= kPlaneLds) {
         const uint32_t per = s2_planes(H, W, planes);
-        const bool full = pad == 0 && 2 * (P - 1) + R <= H && 2 * (Q - 1) + R <= W;
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((planes + per - 1) / per), dim3(256),
                                (per * lds + 15) / 16 * 16, stream, x, y, max_mode ? mask : nullptr,
@@ -462,7 +469,7 @@ hipError_t launch_pool_bwd(bool max_mode, const float *dy, const int *mask, floa
     const uint32_t total = (uint32_t)((long long)N * C * H * W);
     const uint32_t planes = (uint32_t)((long long)N * C);
     const size_t lds = (size_t)P * Q * (max_mode ? 2 : 1) * sizeof(float);
-    if (s2_applies(R, S, stride, pad) && lds <= kPlaneLds) {
+    if (s2_applies(R, S, stride, pad, H, W, planes, false) && lds <= kPlaneLds) {
         const uint32_t per = s2_planes(H, W, planes);
         const int A = (H + pad + 1) / 2, B = (W + pad + 1) / 2;
         const size_t bytes = ((size_t)per * P * Q * sizeof(float) + 15) / 16 * 16;

@@ -101,8 +101,9 @@ def test_pool_random_shapes(mode, pshape):
 
 
 # 2 x 2 and 3 x 3 windows at stride 2 have kernels of their own: several small
-# planes a workgroup (about 1024 elements), planes up to 48 KiB, windows all
-# inside the image or not, words past a multiple of four.
+# planes a workgroup (about 1024 elements; from 2^19 elements on, fewer only
+# forward and 3 x 3 inside the image), planes up to 48 KiB, windows all inside the
+# image or not, words past a multiple of four.
 @pytest.mark.parametrize("mode", ["max", "avg"])
 @pytest.mark.parametrize("pshape", [
     (3, 7, 13, 13, 3, 3, 2, 0),     # six planes a workgroup, a ragged last one
@@ -116,6 +117,13 @@ def test_pool_random_shapes(mode, pshape):
     (1, 2, 110, 111, 3, 3, 2, 0),   # the largest planes of the forward kernel
     (1, 2, 110, 111, 2, 2, 2, 1),
     (1, 2, 112, 112, 2, 2, 2, 0),   # larger: forward per element, backward here
+    (7, 451, 13, 13, 3, 3, 2, 0),   # small planes from here on
+    (7, 443, 13, 13, 3, 3, 2, 1),   # just below 2^19 elements
+    (1, 4682, 14, 8, 2, 2, 2, 1),   # just above
+    (3, 29301, 3, 2, 2, 2, 2, 0),
+    (2, 270001, 1, 1, 2, 2, 2, 1),
+    (1, 175003, 3, 1, 3, 3, 2, 2),
+    (1, 5, 5, 3, 3, 3, 2, 0),       # forward: all planes in one workgroup
 ], ids=str)
 def test_stride_2_windows(mode, pshape):
     N, C, H, W, R, S, st, pad = pshape
