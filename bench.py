@@ -222,6 +222,12 @@ class LayerRun:
         return names[i].startswith("fast filtering") or (
             i == 0 and any(s.endswith("products summed directly") for s in names))
 
+    def executed(self, p):
+        """Share of a direct sum's multiplications that the pass's plan executes:
+        16 of 36 by fast filtering, 64 of 100 with 5x5 filters (on whole 2x2
+        tiles).  Rooflines count these."""
+        return (16 / 36 if self.L.shape[5] == 3 else 64 / 100) if self.fast(p) else 1.0
+
     def run(self, p):
         fn, args = self.calls[p]
         st = fn(*args)
@@ -360,17 +366,23 @@ def kernel_time(run, p, reps, hev):
 
 
 TRAFFIC_DIR = os.path.join(ROOT, "profiles")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1903_06934_amd", "csrc", "conv_kernels.hip")
+CSRC = os.path.join(ROOT, "paper_1903_06934_amd", "csrc")
+
+
+def kernel_source(plan):
+    """The file with the GEMM of a plan (as LayerRun.plan names it)."""
+    return os.path.join(CSRC, "wino_kernels.hip" if ": fast filtering" in plan
+                        else "conv_kernels.hip")
 
 
 def measured_traffic(cfg, layer, p, plan):
     """HBM bytes per launch of the (cfg, layer, pass) GEMM from a committed
     rocprofv3 counter summary (profiles/traffic_*.txt), if one exists for
     exactly this workload and plan and the kernel source has not changed
-    since."""
+    since.  Fast filtering is one plan, whether the rule or the list runs it."""
     import glob
     import hashlib
-    sha = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()
+    sha = hashlib.sha256(open(kernel_source(plan), "rb").read()).hexdigest()
     for f in sorted(glob.glob(os.path.join(TRAFFIC_DIR, "traffic_*.txt"))):
         kv = {}
         for line in open(f):
@@ -378,7 +390,9 @@ def measured_traffic(cfg, layer, p, plan):
                 k, v = line.split(":", 1)
                 kv[k.strip()] = v.strip()
         if (kv.get("workload") == f"{cfg}:{layer}:{p}" and kv.get("kernel_source_sha256") == sha
-                and kv.get("plan") == plan and "traffic_bytes_per_launch" in kv):
+                and (kv.get("plan") == plan or
+                     ": fast filtering" in plan and ": fast filtering" in kv.get("plan", ""))
+                and "traffic_bytes_per_launch" in kv):
             return float(kv["traffic_bytes_per_launch"])
     return None
 
@@ -529,7 +543,8 @@ def _bench_config(cfg, args, with_cpu):
             med, mn = time_call(lambda: r.run(p), args.reps)
             F = flops_of(L)
             B = bytes_of(L, p)
-            t_roof = max(F / (PEAK_TFLOPS * 1e12), B / (PEAK_GBS * 1e9)) * 1e3
+            Fx = F * r.executed(p) if F else 0.0
+            t_roof = max(Fx / (PEAK_TFLOPS * 1e12), B / (PEAK_GBS * 1e9)) * 1e3
             in_stack = not (p == "bwd_data" and L.first)
             row = {"layer": L.name, "pass": p, "count": L.count, "in_stack": in_stack,
                    "cache": "warm", "ms": round(med, 4), "ms_min": round(mn, 4),
@@ -556,11 +571,7 @@ def _bench_config(cfg, args, with_cpu):
     F = flops_of(drun.L)
     ai = F / bytes_of(drun.L, dom["pass"])
     if ai >= ridge:
-        # Fast filtering executes 16 of a direct sum's 36 multiplications, 64
-        # of 100 with 5x5 filters (on whole 2x2 tiles): the roofline counts
-        # what is executed.
-        fast = getattr(drun, "fast", lambda p: False)(dom["pass"])
-        ach = F * ((16 / 36 if drun.L.shape[5] == 3 else 64 / 100) if fast else 1) / k_ms / 1e9
+        ach = F * drun.executed(dom["pass"]) / k_ms / 1e9
         roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(ach / PEAK_TFLOPS, 4), "traffic": None}
     else:
