@@ -250,8 +250,9 @@ __device__ __forceinline__ void store_tile(const WinoArgs &a, const TileAt &at, 
 // reads of consecutive lanes.
 //
 // What bounds it: on gfx950 a VALU instruction does not run beside an fp32
-// MFMA of its SIMD (measured: one v_add after every MFMA takes 39 cycles a
-// pair instead of 32, six 50), so the transform's additions cost MFMA time;
+// MFMA of its SIMD (measured with two waves a SIMD: one v_add after every MFMA
+// takes 39 cycles a pair instead of 32, six 51), so the transform's additions cost
+// MFMA time (128 channels on 112 x 112: 0.70 MFMA-busy, no LDS conflicts);
 // sharing V between the two channel halves halves them (a first version with
 // the transform in every wave, two workgroups of four waves a CU, ran its
 // steady state at 0.76 of the MFMA rate), and they run in one burst.
@@ -764,7 +765,8 @@ __global__ __launch_bounds__(256) void wino_filter_kernel(const WinoArgs a, floa
 namespace {
 
 constexpr int WG_Q = 272;               // words of one (step, block, q): 4 rows of 16 lanes, 68 apart,
-constexpr int WG_STEP = 16 * WG_Q + 16; // so that the eight tiles' writes hit distinct banks
+constexpr int WG_STEP = 16 * WG_Q + 16; // for distinct banks in the eight tiles' writes (the counters
+                                        // still show 3 conflict cycles an LDS instruction)
 constexpr int WG_STG = 2 * WG_STEP;
 constexpr int WG_SLAB = 64 * 64 * 9 + 64;  // words: [k][c][tap], then the bias gradient
 
