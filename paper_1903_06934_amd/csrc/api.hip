@@ -563,6 +563,38 @@ bool wino_applies(const Geom &g, int M, int cin)
            (long long)wino_filter_words(M, cin, g.G, g.R) <= kMaxChunkElems;
 }
 
+// Stages of the longest workgroup.
+double wino_stages(const WinoWork &w)
+{
+    return (double)w.rounds * w.nstage + ((long long)w.rest * w.nstage + w.nwg - 1) / w.nwg;
+}
+
+// Whether a direct 5 x 5 plan that is split over the reduction is estimated faster
+// than fast filtering.  Fitted (us) to 2800 such layers, batch 1 to 128, 48 to 512
+// channels, maps of 4 to 112; both estimates within 10 % of nine in ten.  510 of
+// them were slower by fast filtering (3 % and more, worst 0.64); of those left to
+// it 22 are (worst 0.93), and 104 of the others would be faster by it.
+bool split_beats_wino(const Geom &g, int M, int cin, int Pout, int Qout, const ImgPlan &direct)
+{
+    if (direct.halo >= 0 || direct.nsplit == 1 || cin % 16)  // (unaligned channels: 0.97 and more)
+        return false;
+    const double cus = num_cus();
+    const WinoWork w = wino_plan(M, cin, g.G, g.R, g.N, Pout, Qout, num_cus());
+    const double stages = wino_stages(w);
+    double fast = 12.7 + 2.06 * stages;  // us
+    if (w.rounds == 0)
+        fast += 0.35 * w.nwg / w.rest + 0.026 * w.nwg;  // parts of a tile, slabs
+    int bm, bn;
+    img_tile_dims(direct.tile, bm, bn);
+    const long long cols = (long long)g.N * Pout * Qout;
+    const double wgs = tile_count(direct.tile, M, cols, g.G) * direct.nsplit / cus;
+    const double slices = cin * g.R * g.S / 16.0 / direct.nsplit;
+    const double us = (bm > 64 ? 14 : 3) +
+                      slices * (0.55 + 0.23 * std::max(0.0, wgs - 1) * bm * bn / 4096) +
+                      4.5e-6 * direct.nsplit * cols * g.G * M;
+    return us < fast;
+}
+
 // The built-in rule's use of it.  Its GEMM runs in stages (64 rows x 64 tiles
 // x 8 channels); below some number of them its three launches cost more than
 // the direct plan's two, unless the reduction is long, which the direct plans
@@ -577,19 +609,19 @@ bool wino_applies(const Geom &g, int M, int cin)
 // 1.4-1.5.  Fewer than 32 rows leave most of a 64-row tile idle; with fewer
 // than 32 channels the transforms' rounding is no longer small beside the
 // sums' (error against 64 bits at 16 channels: equal to the direct plans').
-// With 65 rows or 32 half of a tile is empty: 0.86-1.8 with 3 to 3.7 full tiles'
-// worth of stages a CU, 0.98-1.9 from 4 on; 32 rows of up to 64 channels 0.86-1.1
-// below 8, 1.1-1.8 from there.
+// Layers of 32 rows and up to 96 channels that the direct image GEMM takes by
+// its 32-row tile, where half of this one's is empty: 0.86-0.93 (one 1.4) below 5
+// full tiles' worth of stages a CU, 0.98-1.8 from there.
 // 5 x 5 layers (16 multiplications of 25, so less to gain) take it from 64
 // channels and 48 rows on, or 48 channels and 12 stages a CU: AlexNet conv2 (48
 // to 128 channels a group, 27 x 27, batch 128) 1.20 forward, 1.25 backward-data;
 // 64 to 192 channels on 28 x 28 and 56 x 56 maps 1.2-1.9; 64 to 128 channels on one
 // or four images of 4 x 4 to 28 x 28 2.2-3.1 (128 -> 128 1.0-1.2); 48 to 128 on 14 x
-// 14 (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.  Not where few
-// tiles of a long reduction are cut in 16 parts and more, which its last launch
-// adds one after another, and the direct image GEMM is split as well: 0.64-1.4
-// (464 -> 48 channels on 8 x 47, batch 6: 34 / 53 us), with fewer parts 0.89-1.9
-// (five of 1600 layers below 0.97).
+// 14 (9 stages a CU) 0.95; 16 or 32 channels or rows 0.65-0.98.  Where the direct
+// plan is an image GEMM split over the reduction, its time and fast filtering's
+// are estimated (split_beats_wino): few tiles cut in many parts, which fast
+// filtering's last launch adds one after another, are 0.64-1.0 (464 -> 48 channels
+// on 8 x 47, batch 6: 34 / 53 us).
 bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout, const ImgPlan &direct)
 {
     if (cin < 32 || M < 32 || !wino_applies(g, M, cin))
@@ -599,13 +631,13 @@ bool wino_rule(const Geom &g, int M, int cin, int Pout, int Qout, const ImgPlan 
     if (g.R == 5) {
         if (M < 48 || cin < 48 || (cin < 64 && row * 4 * ((M + 63) / 64) < 12 * num_cus()))
             return false;
-        const WinoWork w = wino_plan(M, cin, g.G, g.R, g.N, Pout, Qout, num_cus());
-        return direct.halo >= 0 || direct.nsplit == 1 || w.rounds > 0 || w.nwg < 16 * w.rest;
+        return !split_beats_wino(g, M, cin, Pout, Qout, direct);
     }
     if (cin >= 128 && M >= 64)
         return true;
-    return row * ((M + 63) / 64) >= 6 * num_cus() &&
-           row * M >= (M < 48 && cin <= 64 ? 8 : 4) * 64 * num_cus();
+    if (direct.halo < 0 && direct.tile == IMG_32x64 && cin <= 96 && row * M < 5 * 64 * num_cus())
+        return false;
+    return row * ((M + 63) / 64) >= 6 * num_cus();
 }
 
 // The flag, the transformed filters, the slabs of cut tiles.
@@ -1310,43 +1342,6 @@ size_t wgrad_wino_ws(const Geom &g)
         wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, g.N, g.P, g.Q, num_cus(), &cw)));
 }
 
-// The built-in rule's use of it: where its 64 x 64 tiles are mostly real, a tile
-// has at least 32 stages (of eight 2 x 2 tiles of dy) to reduce, and the layer's
-// products fill at least 7 stages a CU, 11 on maps of odd width (whose loads are
-// of single words).  Measured on the MI355X (direct / fast time): VGG-16
-// conv1_2 ... conv4_3 at batch 32 1.6-1.9, conv5_x 1.5; ResNet-50's 3 x 3
-// layers at batch 64 1.2-1.5; AlexNet conv3-conv5 1.4-1.5; 512 channels on 14 x
-// 14 maps 0.84 at batch 4 (24 stages a tile), 1.27 at batch 16; half-empty tiles
-// (32 -> 64 channels) 0.93-1.0, 16 -> 16 0.6-0.8.  1300 layers of 32 to 512 channels
-// a group, batch 1 to 128, maps of 4 to 112: 0.64-1.3 with fewer stages' worth
-// (the stages are then mostly padding, and the slabs' sums not small beside
-// them), else 0.92-2.4, three below 0.97.  Where a stage's two columns of four images (a strided
-// load each) meet tiles that are a quarter empty, which the direct 48-channel
-// tiles are not (odd widths), or a single block of fewer than 64 (even ones):
-// 0.86-1.3 (48 -> 64 channels on 53 x 34, batch 37: 50 / 59 us).
-// 5 x 5 layers (the four parts of the filter count as tiles) on maps of an even
-// width where the products fill three quarters of a part's stages and 18 a CU:
-// 1.05-1.5 (one of 60 0.87); AlexNet conv2 (27 x 27) 0.89, fuller or longer ones 0.77-1.2,
-// else 0.34-1.2 (384 -> 288 channels on 10 x 6, batch 74: 92 / 159 us).
-bool wgrad_wino_rule(const Geom &g)
-{
-    if (!wgrad_wino_applies(g))
-        return false;
-    int cw;
-    const WinoWork w = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, g.N, g.P, g.Q, num_cus(), &cw);
-    const long long kb = (g.Kg + 63) / 64, cb = (g.Cg + 63) / 64, full = 4096 * kb * cb;
-    const long long channels = (long long)g.Kg * g.Cg;
-    if (10 * channels < 6 * full || w.nstage < 32)
-        return false;
-    // The products in stages of 64 x 64 channels and 32 pixels.
-    const long long real = channels * g.G * ((long long)g.N * g.P * g.Q) / (4096 * 32);
-    if (g.R == 5)
-        return g.W % 2 == 0 && real >= 18 * num_cus() && 4 * real >= 3 * (kb * cb * g.G * w.nstage);
-    if (real < (g.W % 2 ? 11 : 7) * num_cus())
-        return false;
-    return cw > 2 || (g.W % 2 ? 4 * channels > 3 * full : g.Kg >= 64 && g.Cg >= 64);
-}
-
 WgradPlan wgrad_direct_rule(const Geom &g)
 {
     // Where the channels allow, 64 x 32 tiles over eight waves: on maps of 112
@@ -1376,10 +1371,68 @@ WgradPlan wgrad_direct_rule(const Geom &g)
     return p;
 }
 
+// Times of backward-weight in us, to choose between the direct rule's plan and
+// fast filtering.  Fitted to 3800 layers (3 x 3 and 5 x 5, batch 1 to 128, 39 to 512
+// channels a group, maps of 4 to 112): within 12 % for nine in ten.
+// Direct: products of the tiles a CU, the length of a workgroup's chain, the sums
+// of the splits.
+double wgrad_direct_us(const Geom &g, const WgradPlan &p)
+{
+    const double weights = (double)g.K * g.Cg * g.R * g.S, sums = 2.9e-6 * p.nsplit * weights;
+    int bm = 64, bn = 16 * p.halo_ct;
+    if (!p.halo_tw)
+        wgrad_tile_dims(p.tile, bm, bn);
+    const int taps = g.R * g.S;
+    const double tiles = (double)g.G * ((g.Kg + bm - 1) / bm) * ((g.Cg + bn - 1) / bn) * taps;
+    const double work = tiles * bm * bn * p.nsplit * 256 / num_cus();
+    if (p.halo_tw)  // chunk: blocks of 112 pixels
+        return 2.3 + (p.halo_ct == 1 ? 0.74e-6 : 0.86e-6) * work * p.chunk + 6.8 * p.chunk + sums;
+    const double slices = p.chunk / 64.0;
+    return 11 + 1.01e-6 * work * slices + 0.66 * slices + sums;
+}
+
+// Fast filtering: its stages a CU, dearer with single-word loads (odd widths) and
+// with fewer columns of more images a stage, whose loads touch more cache lines
+// the wider the map; the sums and stores of the output tiles.
+double wgrad_wino_us(const Geom &g, const WinoWork &w, int cw, long long tiles)
+{
+    const double us = cw == 8   ? (g.W % 2 ? 2.6 : 2.35)
+                      : cw == 4 ? (g.W % 2 ? 3.0 : 2.4)
+                                : (g.W % 2 ? 2.75 : 2.25) + g.W / 72.0;
+    return 22 + us * wino_stages(w) + 0.45 * tiles;
+}
+
+// The built-in rule's use of it: where its 64 x 64 tiles are mostly real, a tile
+// has at least 32 stages (of eight 2 x 2 tiles of dy) to reduce, there are at
+// least 6 stages a CU (16 with 5 x 5 filters, whose four parts count as tiles, on
+// maps of an even width only), and by the estimates above.  Measured on the MI355X
+// (direct / fast time): VGG-16 conv1_2 ... conv4_3 at batch 32 1.6-1.9, conv5_x 1.5;
+// ResNet-50's 3 x 3 layers at batch 64 1.2-1.5; AlexNet conv3-conv5 1.4-1.5; 512
+// channels on 14 x 14 maps 0.84 at batch 4 (24 stages a tile), 1.27 at batch 16;
+// half-empty tiles (32 -> 64 channels) 0.93-1.0, 16 -> 16 0.6-0.8; 5 x 5 layers of 64
+// to 192 channels on 28 x 28 and 56 x 56 maps 1.24-1.5, AlexNet conv2 (27 x 27) 0.89.
+// Of the 3800 layers above, 441 were up to three times slower by fast filtering (457
+// -> 416 channels on one 77 x 6 map 44 / 69 us; 5 x 5, 384 -> 288 on 10 x 6, batch 74,
+// 92 / 159), with the estimates 61, the worst 0.84; 68 of those then left to the
+// direct plan would have gained more than 3 %.
+bool wgrad_wino_rule(const Geom &g, const WgradPlan &direct)
+{
+    if (!wgrad_wino_applies(g) || (g.R == 5 && g.W % 2))
+        return false;
+    int cw;
+    const WinoWork w = wino_wgrad_plan(g.Kg, g.Cg, g.G, g.R, g.N, g.P, g.Q, num_cus(), &cw);
+    const long long kb = (g.Kg + 63) / 64, cb = (g.Cg + 63) / 64;
+    const long long tiles = kb * cb * g.G * (g.R == 5 ? 4 : 1);
+    if (10LL * g.Kg * g.Cg < 6 * 4096 * kb * cb || w.nstage < 32 ||
+        tiles * w.nstage < (g.R == 5 ? 16 : 6) * num_cus())
+        return false;
+    return wgrad_wino_us(g, w, cw, tiles) < wgrad_direct_us(g, direct);
+}
+
 WgradPlan wgrad_rule(const Geom &g)
 {
     WgradPlan p = wgrad_direct_rule(g);
-    if (wgrad_wino_rule(g))
+    if (wgrad_wino_rule(g, p))
         p.wino = WINO_RULE;
     return p;
 }
